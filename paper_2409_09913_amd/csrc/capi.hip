@@ -27,7 +27,11 @@ hipError_t launch_pack_n(const uint8_t* codes, const int64_t* list_off, const in
                          int64_t nlist, int dp, int bits, int64_t ntiles, uint8_t* packed, hipStream_t st);
 hipError_t launch_unpack_n(const uint8_t* packed, const int64_t* list_off, const int64_t* tile_off,
                            int64_t nlist, int dp, int bits, int64_t ntiles, uint8_t* codes, hipStream_t st);
-hipError_t launch_count(const int32_t* assign, int64_t n, int64_t nlist, int32_t* cnt, int32_t* bad, hipStream_t st);
+hipError_t launch_norm(const float* X, int64_t n, int K, float* n2, hipStream_t st);
+size_t assign_scratch_bytes(int64_t n, int64_t N);
+hipError_t launch_assign(const float* A, int64_t n, int K, const unsigned short* Bh, const unsigned short* Bl,
+                         int64_t N, const float* an2, const float* bn2, int neg_ip, int32_t* out, void* scratch,
+                         hipStream_t st);
 
 static thread_local std::string g_err;
 
@@ -292,47 +296,29 @@ int probe_impl(const float* q, int64_t nq, const float* cent, int64_t nlist, int
     return ERQ_OK;
 }
 
-// ---- k-means (Sec. 4.1 builds the IVF lists with KMeans) -------------------------
-// nearest centroid of every row (the probe with nprobe = 1: ties to the lower
-// centroid id), in row chunks that keep the n x C distances small
-int assign_rows(const float* x, int64_t n, int dp, const float* cent, int64_t C, int32_t* asg, hipStream_t st)
-{
-    if (n <= 0) return ERQ_OK;
-    const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(n, (int64_t)(1LL << 28) / C));
-    void* pws = nullptr;
-    const size_t pb = probe_ws(chunk, C, dp);
-    ERQ_HIP(hipMalloc(&pws, pb));
-    struct Free { void* p; ~Free() { hipFree(p); } } fr{pws};
-    for (int64_t r0 = 0; r0 < n; r0 += chunk) {
-        const int64_t m = std::min(chunk, n - r0);
-        if (int rc = probe_impl(x + r0 * dp, m, cent, C, dp, 1, asg + r0, nullptr, pws, pb, st)) return rc;
+// One device allocation cut into 256-byte aligned pieces: a first walk with no
+// base adds the sizes up, the second one hands the pieces out.  Allocations of
+// a build or a k-means are few and small: device memory given back and taken
+// again is cleared by the driver at some 40 GB/s, so calls in a row that
+// allocate gigabytes wait for that rather than for their kernels.
+struct Carve {
+    char* base = nullptr;
+    size_t used = 0;
+    template <class T>
+    void take(T** out, size_t count) {
+        if (base) *out = (T*)(base + used);
+        used += align256(sizeof(T) * count);
     }
-    return ERQ_OK;
-}
+};
 
-// per-list counts of an assignment -> host list offsets (ERQ_EINVAL for ids outside [0, C))
-int list_offsets(const int32_t* asg, int64_t n, int64_t C, std::vector<int64_t>& off, hipStream_t st)
-{
-    int32_t* aux = nullptr;
-    ERQ_HIP(hipMalloc(&aux, sizeof(int32_t) * (C + 1)));
-    struct Free { void* p; ~Free() { hipFree(p); } } fr{aux};
-    hipLaunchKernelGGL(fill_i32, dim3(blocks(C + 1)), dim3(256), 0, st, aux, C + 1, 0);
-    ERQ_HIP(launch_count(asg, n, C, aux, aux + C, st));
-    std::vector<int32_t> hc(C + 1);
-    ERQ_HIP(hipMemcpyAsync(hc.data(), aux, sizeof(int32_t) * (C + 1), hipMemcpyDeviceToHost, st));
-    ERQ_HIP(hipStreamSynchronize(st));
-    if (hc[C] != 0) return fail(ERQ_EINVAL, "assignment outside [0, nlist)");
-    off.assign(C + 1, 0);
-    for (int64_t l = 0; l < C; ++l) off[l + 1] = off[l] + hc[l];
-    return ERQ_OK;
-}
-
+// ---- k-means (Sec. 4.1 builds the IVF lists with KMeans) -------------------------
 // Lloyd's algorithm.  Readings: the initial centroids are C distinct rows
 // chosen by Floyd's sampling with Philox random numbers of the seed (taken in
-// ascending row order); `iters` rounds of assignment then per-list means; an
+// ascending row order); `iters` rounds of assignment (nearest centroid, the
+// probe's distances, ties to the lower centroid id) then per-list means; an
 // empty list keeps its centroid; the returned assignment is to the final
 // centroids.  Every sum has a fixed order, so a seed gives the same lists on
-// every run.
+// every run.  The rounds are enqueued without a host round trip.
 int kmeans_impl(const float* x, int64_t n, int dp, int64_t C, int iters, uint64_t seed, float* cent, int32_t* asg_out,
                 hipStream_t st)
 {
@@ -345,38 +331,44 @@ int kmeans_impl(const float* x, int64_t n, int dp, int64_t C, int iters, uint64_
     }
     std::vector<int64_t> rows(pick.begin(), pick.end());
     std::sort(rows.begin(), rows.end());
-    struct Bufs { std::vector<void*> p; ~Bufs() { for (void* q : p) hipFree(q); } } bufs;
-    auto dalloc = [&](size_t b, void** out) -> int {
-        ERQ_HIP(hipMalloc(out, std::max<size_t>(b, 256)));
-        bufs.p.push_back(*out);
-        return ERQ_OK;
+    int64_t *drows = nullptr, *doff = nullptr;
+    int32_t *asg = asg_out, *ids32 = nullptr, *cnt = nullptr, *chunk0 = nullptr;
+    float *xn = nullptr, *cn = nullptr;
+    unsigned short *ch = nullptr, *cl = nullptr;
+    char *bscr = nullptr, *mscr = nullptr, *ascr = nullptr;
+    auto lay = [&](Carve& m) {
+        m.take(&drows, C);
+        m.take(&doff, C + 1);
+        if (!asg_out) m.take(&asg, n);
+        m.take(&ids32, n);
+        m.take(&cnt, C);
+        m.take(&chunk0, C + 1);
+        m.take(&xn, n);
+        m.take(&cn, C);
+        m.take(&ch, (size_t)C * dp);
+        m.take(&cl, (size_t)C * dp);
+        m.take(&bscr, bucket_scratch_bytes(n, C));
+        m.take(&mscr, list_mean_scratch_bytes(n, C, dp));
+        m.take(&ascr, assign_scratch_bytes(n, C));
     };
-    int64_t* drows = nullptr; int32_t* asg = asg_out; int32_t* ids32 = nullptr; int64_t* doff = nullptr;
-    void* bscr = nullptr;
-    if (int rc = dalloc(sizeof(int64_t) * C, (void**)&drows)) return rc;
-    if (!asg) {
-        if (int rc = dalloc(sizeof(int32_t) * n, (void**)&asg)) return rc;
-    }
-    if (int rc = dalloc(sizeof(int32_t) * n, (void**)&ids32)) return rc;
-    if (int rc = dalloc(sizeof(int64_t) * (C + 1), (void**)&doff)) return rc;
-    if (int rc = dalloc(bucket_scratch_bytes(n, C), &bscr)) return rc;
+    Carve size, mem;
+    lay(size);
+    ERQ_HIP(hipMalloc(&mem.base, size.used));
+    struct Free { void* p; ~Free() { hipFree(p); } } fr{mem.base};
+    lay(mem);
     ERQ_HIP(hipMemcpyAsync(drows, rows.data(), sizeof(int64_t) * C, hipMemcpyHostToDevice, st));
     ERQ_HIP(launch_gather_rows(x, dp, drows, C, cent, st));
-    ERQ_HIP(hipStreamSynchronize(st));                   // rows goes out of scope
-    std::vector<int64_t> off;
-    for (int it = 0; it < iters; ++it) {
-        if (int rc = assign_rows(x, n, dp, cent, C, asg, st)) return rc;
-        if (int rc = list_offsets(asg, n, C, off, st)) return rc;
-        ERQ_HIP(hipMemcpyAsync(doff, off.data(), sizeof(int64_t) * (C + 1), hipMemcpyHostToDevice, st));
-        ERQ_HIP(launch_bucket_sort(asg, n, C, doff, ids32, bscr, st));
-        void* mscr = nullptr;
-        ERQ_HIP(hipMalloc(&mscr, list_mean_scratch_bytes(off, dp)));
-        const hipError_t e = launch_list_mean(x, dp, ids32, off, doff, cent, mscr, st);   // synchronises
-        hipFree(mscr);
-        ERQ_HIP(e);
+    ERQ_HIP(launch_norm(x, n, dp, xn, st));
+    for (int it = 0; it <= iters; ++it) {
+        ERQ_HIP(launch_split_norm(cent, C, dp, ch, cl, cn, st));
+        ERQ_HIP(launch_assign(x, n, dp, ch, cl, C, xn, cn, 0, asg, ascr, st));
+        if (it == iters) break;
+        ERQ_HIP(launch_bucket_count(asg, n, C, cnt, nullptr, bscr, st));
+        ERQ_HIP(launch_list_prefix(cnt, C, doff, chunk0, st));
+        ERQ_HIP(launch_bucket_place(asg, n, C, doff, ids32, bscr, st));
+        ERQ_HIP(launch_list_mean(x, n, dp, ids32, doff, C, chunk0, cent, mscr, st));
     }
-    if (int rc = assign_rows(x, n, dp, cent, C, asg, st)) return rc;
-    ERQ_HIP(hipStreamSynchronize(st));
+    ERQ_HIP(hipStreamSynchronize(st));                   // the scratch and `rows` go out of scope
     return ERQ_OK;
 }
 
@@ -865,32 +857,46 @@ int erq_index_build(erq_index ix, const float* x, int64_t n, const float* centro
     ERQ_HIP(alloc_cent_planes(ix, st));
     ERQ_HIP(launch_gemm(ix->cent, C, dp, ix->P, dp, 0, 0, ix->cent_rot, dp, st));
 
+    // scratch: the assignment and its sort, the unpacked codes, and the
+    // residuals and rotated rows of one batch (64 MB of each: 768 tiles of the
+    // rotation's GEMM and more at every width)
+    const int64_t bt = std::max<int64_t>(
+        1, std::min<int64_t>(n, std::max<int64_t>(4096, ((int64_t)64 << 20) / (4 * dp) / 128 * 128)));
+    int32_t *asg = nullptr, *cnt = nullptr, *bad = nullptr, *ids32 = nullptr;
+    float *xn = nullptr, *res = nullptr, *rot = nullptr, *nrm = nullptr, *l1 = nullptr;
+    uint8_t *codes_u = nullptr, *mu = nullptr;
+    char *bs = nullptr, *as = nullptr;
+    auto lay = [&](Carve& m) {
+        m.take(&asg, n);
+        m.take(&cnt, C);
+        m.take(&bad, 1);
+        m.take(&ids32, n);
+        m.take(&bs, bucket_scratch_bytes(n, C));
+        if (!assign) { m.take(&xn, n); m.take(&as, assign_scratch_bytes(n, C)); }
+        m.take(&codes_u, (size_t)n * dc);
+        m.take(&res, (size_t)bt * dp);
+        m.take(&rot, (size_t)bt * dc);
+        m.take(&nrm, bt);
+        if (ix->two_stage) { m.take(&l1, n); m.take(&mu, (size_t)n * dc); }
+    };
+    Carve size, mem;
+    lay(size);
+    ERQ_HIP(hipMalloc(&mem.base, size.used));
+    struct Free { void* p; ~Free() { hipFree(p); } } fr{mem.base};
+    lay(mem);
+
     // assignment (nearest centroid when not given)
-    int32_t* asg = nullptr;
-    int32_t* aux = nullptr;     // cnt | (unused) | bad
-    ERQ_HIP(hipMalloc(&asg, sizeof(int32_t) * std::max<int64_t>(n, 1)));
-    ERQ_HIP(hipMalloc(&aux, sizeof(int32_t) * (2 * C + 1)));
-    struct Guard { std::vector<void*> p; ~Guard() { for (void* q : p) hipFree(q); } } guard;
-    guard.p.push_back(asg); guard.p.push_back(aux);
     if (assign) {
         ERQ_HIP(hipMemcpyAsync(asg, assign, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, st));
     } else if (n > 0) {
-        const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(n, (int64_t)(1LL << 28) / C));
-        void* pws = nullptr;
-        size_t pb = probe_ws(chunk, C, dp);
-        ERQ_HIP(hipMalloc(&pws, pb));
-        guard.p.push_back(pws);
-        for (int64_t r0 = 0; r0 < n; r0 += chunk) {
-            int64_t m = std::min(chunk, n - r0);
-            if (int rc = probe_impl(x + r0 * dp, m, ix->cent, C, dp, 1, asg + r0, nullptr, pws, pb, st, ProbePre(),
-                                    ix->metric))
-                return rc;
-        }
+        int pr = prof_begin(PK_PROBE, st);
+        ERQ_HIP(launch_norm(x, n, dp, xn, st));
+        ERQ_HIP(launch_assign(x, n, dp, ix->cent_hi, ix->cent_lo, C, xn, ix->cent_n2, ix->metric != ERQ_METRIC_L2, asg,
+                              as, st));
+        prof_end(pr, st);
     }
-    int32_t* cnt = aux;
-    int32_t* bad = aux + 2 * C;
-    hipLaunchKernelGGL(fill_i32, dim3(blocks(2 * C + 1)), dim3(256), 0, st, aux, 2 * C + 1, 0);
-    ERQ_HIP(launch_count(asg, n, C, cnt, bad, st));
+    hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, st, bad, 1, 0);
+    ERQ_HIP(launch_bucket_count(asg, n, C, cnt, bad, bs, st));
     std::vector<int32_t> hc(C);
     int32_t hbad = 0;
     ERQ_HIP(hipMemcpyAsync(hc.data(), cnt, sizeof(int32_t) * C, hipMemcpyDeviceToHost, st));
@@ -901,9 +907,6 @@ int erq_index_build(erq_index ix, const float* x, int64_t n, const float* centro
     for (int64_t l = 0; l < C; ++l) off[l + 1] = off[l] + hc[l];
     if (int rc = set_list_meta(ix, off, st)) return rc;
     ix->n = n;
-    int32_t* ids32 = nullptr;
-    ERQ_HIP(hipMalloc(&ids32, sizeof(int32_t) * std::max<int64_t>(n, 1)));
-    guard.p.push_back(ids32);
     ERQ_HIP(hipMalloc(&ix->ids, sizeof(int64_t) * std::max<int64_t>(n, 1)));
     ERQ_HIP(hipMalloc(&ix->fac, sizeof(float2) * std::max<int64_t>(n, 1)));
     ERQ_HIP(hipMalloc(&ix->sfac, sizeof(float2) * std::max<int64_t>(n, 1)));
@@ -911,29 +914,12 @@ int erq_index_build(erq_index ix, const float* x, int64_t n, const float* centro
     // members in list order, ids ascending within each list: a stable bucket
     // sort of the rows by list, so the layout is the same on every build
     if (n > 0) {
-        void* bs = nullptr;
-        ERQ_HIP(hipMalloc(&bs, bucket_scratch_bytes(n, C)));
-        guard.p.push_back(bs);
-        ERQ_HIP(launch_bucket_sort(asg, n, C, ix->list_off, ids32, bs, st));
+        ERQ_HIP(launch_bucket_place(asg, n, C, ix->list_off, ids32, bs, st));
         hipLaunchKernelGGL(widen_i32, dim3(blocks(n)), dim3(256), 0, st, ids32, n, ix->ids);
         ERQ_HIP(hipGetLastError());
     }
 
     // residual -> rotate -> quantise, in batches, list order
-    uint8_t* codes_u = nullptr;
-    ERQ_HIP(hipMalloc(&codes_u, std::max<int64_t>(n, 1) * dc));
-    guard.p.push_back(codes_u);
-    const int64_t bt = std::max<int64_t>(1, std::min<int64_t>(n, 131072));
-    float *res = nullptr, *rot = nullptr, *nrm = nullptr;
-    ERQ_HIP(hipMalloc(&res, sizeof(float) * bt * dp));
-    ERQ_HIP(hipMalloc(&rot, sizeof(float) * bt * dc));
-    ERQ_HIP(hipMalloc(&nrm, sizeof(float) * bt));
-    guard.p.push_back(res); guard.p.push_back(rot); guard.p.push_back(nrm);
-    float* l1 = nullptr;                            // ||r'||_1 per member (two-stage scan)
-    if (ix->two_stage) {
-        ERQ_HIP(hipMalloc(&l1, sizeof(float) * std::max<int64_t>(n, 1)));
-        guard.p.push_back(l1);
-    }
     for (int64_t v0 = 0; v0 < n; v0 += bt) {
         int64_t m = std::min(bt, n - v0);
         ERQ_HIP(launch_residual(x, ix->ids + v0, asg, ix->cent, m, dp, res, nrm, st));
@@ -962,9 +948,6 @@ int erq_index_build(erq_index ix, const float* x, int64_t n, const float* centro
                             ix->sfac, st));
     if (ix->two_stage) {
         // the most significant bit planes in the 1-bit tile layout, and the 1-bit factors
-        uint8_t* mu = nullptr;
-        ERQ_HIP(hipMalloc(&mu, std::max<int64_t>(n, 1) * dc));
-        guard.p.push_back(mu);
         ERQ_HIP(hipMalloc(&ix->msb, std::max<int64_t>((int64_t)4 * dc * ix->ntiles, 256)));
         ERQ_HIP(hipMalloc(&ix->fac1, sizeof(float4) * std::max<int64_t>(n, 1)));
         if (n > 0) {

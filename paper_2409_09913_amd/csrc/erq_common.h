@@ -164,18 +164,25 @@ void sample_rotation(int dp, uint64_t seed, float* P);
 // 64 random bits of Philox4x32-10 for (seed, stream tag, counter) (host code)
 uint64_t philox_u64(uint64_t seed, uint32_t tag, uint64_t counter);
 
-// Stable bucket sort of row ids by list: ids32[list_off[l] + j] = the j-th
-// row (ascending) with assign[row] == l.  list_off (device, nlist + 1) must
-// hold the exclusive prefix of the per-list counts.  Scratch: bucket_scratch_bytes.
+// Stable bucket sort of row ids by list, in two steps on the same scratch
+// (bucket_scratch_bytes).  Count: cnt[l] = rows of list l; bad (or null) is set
+// when an id lies outside [0, nlist).  Place: ids32[list_off[l] + j] = the j-th
+// row (ascending) with assign[row] == l, list_off (device, nlist + 1) being
+// the exclusive prefix of cnt; every id must be valid.
 size_t bucket_scratch_bytes(int64_t n, int64_t nlist);
-hipError_t launch_bucket_sort(const int32_t* assign, int64_t n, int64_t nlist, const int64_t* list_off,
-                              int32_t* ids32, void* scratch, hipStream_t st);
+hipError_t launch_bucket_count(const int32_t* assign, int64_t n, int64_t nlist, int32_t* cnt, int32_t* bad,
+                               void* scratch, hipStream_t st);
+hipError_t launch_bucket_place(const int32_t* assign, int64_t n, int64_t nlist, const int64_t* list_off,
+                               int32_t* ids32, void* scratch, hipStream_t st);
+// Exclusive prefixes of the counts (list_off) and of their mean chunks
+// (chunk0), nlist + 1 of each, on the device.
+hipError_t launch_list_prefix(const int32_t* cnt, int64_t nlist, int64_t* list_off, int32_t* chunk0, hipStream_t st);
 // Per-list means of x over the members of each list (rows ids32 in list
 // order, FP64 sums in member order), into cent (FP32); empty lists keep
 // their row of cent.  Scratch: list_mean_scratch_bytes.
-size_t list_mean_scratch_bytes(const std::vector<int64_t>& off, int dp);
-hipError_t launch_list_mean(const float* x, int dp, const int32_t* ids32, const std::vector<int64_t>& off,
-                            const int64_t* list_off, float* cent, void* scratch, hipStream_t st);
+size_t list_mean_scratch_bytes(int64_t n, int64_t nlist, int dp);
+hipError_t launch_list_mean(const float* x, int64_t n, int dp, const int32_t* ids32, const int64_t* list_off,
+                            int64_t nlist, const int32_t* chunk0, float* cent, void* scratch, hipStream_t st);
 hipError_t launch_gather_rows(const float* x, int dp, const int64_t* rows, int64_t m, float* out, hipStream_t st);
 
 // list building

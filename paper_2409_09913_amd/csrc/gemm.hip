@@ -6,6 +6,8 @@
 // 32 x 32 MFMA.  FP32: v_mfma_f32_32x32x2_f32, K staged 16 at a time.
 // BF16: v_mfma_f32_32x32x16_bf16 with FP32 accumulation, K staged 32 at a
 // time, inputs rounded to BF16 (nearest even) while staging.
+#include <algorithm>
+
 #include "erq_common.h"
 
 namespace erq {
@@ -353,8 +355,9 @@ hipError_t launch_gemm_bf16x3(const unsigned short* Ah, const unsigned short* Al
 }
 
 // Rows of X (n x K, K a multiple of 4) -> their BF16 hi/lo planes (as
-// split_bf16_kernel) and squared norms ||x||^2 (FP32); one wave per row,
-// 4 consecutive elements per lane
+// split_bf16_kernel; not with PLANES = false) and squared norms ||x||^2 (FP32);
+// one wave per row, 4 consecutive elements per lane
+template <bool PLANES>
 __global__ __launch_bounds__(256) void split_norm_kernel(const float* __restrict__ X, int64_t n, int K,
                                                          unsigned short* __restrict__ hi,
                                                          unsigned short* __restrict__ lo, float* __restrict__ n2)
@@ -371,11 +374,15 @@ __global__ __launch_bounds__(256) void split_norm_kernel(const float* __restrict
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             s += xv[c] * xv[c];
-            h[c] = f2bf(xv[c]);
-            l[c] = f2bf(xv[c] - __uint_as_float(h[c] << 16));
+            if constexpr (PLANES) {
+                h[c] = f2bf(xv[c]);
+                l[c] = f2bf(xv[c] - __uint_as_float(h[c] << 16));
+            }
         }
-        *(uint2*)(hi + i) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-        *(uint2*)(lo + i) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
+        if constexpr (PLANES) {
+            *(uint2*)(hi + i) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+            *(uint2*)(lo + i) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
+        }
     }
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
     if (lane == 0) n2[r] = s;
@@ -385,7 +392,16 @@ hipError_t launch_split_norm(const float* X, int64_t n, int K, unsigned short* h
                              hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(split_norm_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, X, n, K, hi, lo, n2);
+    hipLaunchKernelGGL(split_norm_kernel<true>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, X, n, K, hi, lo, n2);
+    return hipGetLastError();
+}
+
+// the squared norms alone (the same sums)
+hipError_t launch_norm(const float* X, int64_t n, int K, float* n2, hipStream_t st)
+{
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(split_norm_kernel<false>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, X, n, K,
+                       (unsigned short*)nullptr, (unsigned short*)nullptr, n2);
     return hipGetLastError();
 }
 
@@ -393,6 +409,208 @@ hipError_t launch_split_bf16(const float* x, int64_t n, unsigned short* hi, unsi
 {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(split_bf16_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, st, x, n, hi, lo);
+    return hipGetLastError();
+}
+
+// Nearest column of every row (the assignment of rows to centroids): the
+// smallest of the distances that sqdist_bf16x3_kernel<EPI> would write, ties to
+// the lower column, without writing them.  A is read as FP32 and split into its
+// BF16 planes on the way to LDS (the same values as split_bf16_kernel's).
+//
+// A workgroup takes 128 rows and a range of column tiles; every lane keeps the
+// best of its columns for its 32 rows in registers over the whole range, so the
+// cross-lane work is done once per workgroup.  best (n slots, all ones) holds
+// (key of the distance, column) when the columns are split over gridDim.y > 1
+// workgroups; with one, the columns go straight to out.
+// Bound: LDS traffic and matrix cores, as the probe's GEMM (200,000 x 1024 x
+// 768: 1.18 ms for the product, and the 0.8 GB of distances that the separate
+// selection wrote, allocated and read back (0.84 ms) are gone).
+template <int EPI>
+__global__ __launch_bounds__(256, 2) void assign_bf16x3_kernel(
+    const float* __restrict__ A, int64_t n, int K, const unsigned short* __restrict__ Bhg,
+    const unsigned short* __restrict__ Blg, int N, const float* __restrict__ an2, const float* __restrict__ bn2,
+    int tiles_per_block, unsigned long long* __restrict__ best, int32_t* __restrict__ out)
+{
+    constexpr int BK = 32, LD = BK + 8;
+    __shared__ __align__(16) unsigned short Ah[BM][LD], Al[BM][LD], Bh[BN][LD], Bl[BN][LD];
+    __shared__ float s_an[BM];
+    __shared__ unsigned long long s_best[BM];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int64_t row0 = (int64_t)blockIdx.x * BM;
+    const int wm = (wid >> 1) * 64, wn = (wid & 1) * 64;
+    if (tid < BM) {
+        s_an[tid] = row0 + tid < n && EPI == 1 ? an2[row0 + tid] : 0.0f;
+        s_best[tid] = ~0ull;
+    }
+    // per K-tile: thread tid moves k = 8 (tid % 4) .. + 8 of rows tid/4 and tid/4 + 64
+    const int m0 = tid >> 2, m1 = m0 + 64, kq = (tid & 3) * 8;
+    const bool a0 = row0 + m0 < n, a1 = row0 + m1 < n;
+    const float* pa0 = A + (row0 + m0) * K + kq;
+    const float* pa1 = A + (row0 + m1) * K + kq;
+    const int tile0 = blockIdx.y * tiles_per_block, tile1 = min(tile0 + tiles_per_block, (N + BN - 1) / BN);
+    float bv[2][16];
+    int bc[2][16];                                   // column tile (32 wide) of the best
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { bv[a][r] = __builtin_huge_valf(); bc[a][r] = (tile0 * BN + wn) >> 5; }
+    auto ldf = [](const float* p, bool ok, float4& v0, float4& v1) {
+        v0 = v1 = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (ok) { v0 = *(const float4*)p; v1 = *(const float4*)(p + 4); }
+    };
+    auto put = [](unsigned short* ph, unsigned short* pl, const float4& v0, const float4& v1) {
+        const float x[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+        unsigned h[8], l[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            h[c] = f2bf(x[c]);
+            l[c] = f2bf(x[c] - __uint_as_float(h[c] << 16));
+        }
+        *(uint4*)ph = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+        *(uint4*)pl = make_uint4(l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16));
+    };
+    for (int tile = tile0; tile < tile1; ++tile) {
+        const int col0 = tile * BN;
+        const bool b0 = col0 + m0 < N, b1 = col0 + m1 < N;
+        const unsigned short* pb0h = Bhg + (int64_t)(col0 + m0) * K + kq;
+        const unsigned short* pb1h = Bhg + (int64_t)(col0 + m1) * K + kq;
+        const unsigned short* pb0l = Blg + (int64_t)(col0 + m0) * K + kq;
+        const unsigned short* pb1l = Blg + (int64_t)(col0 + m1) * K + kq;
+        v16f acc[2][2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
+        float4 f0, f1, f2, f3;
+        uint4 r4, r5, r6, r7;
+        auto load = [&](int k) {
+            ldf(pa0 + k, a0, f0, f1);
+            ldf(pa1 + k, a1, f2, f3);
+            r4 = ld16(pb0h + k, b0); r5 = ld16(pb1h + k, b1); r6 = ld16(pb0l + k, b0); r7 = ld16(pb1l + k, b1);
+        };
+        auto store = [&]() {
+            put(&Ah[m0][kq], &Al[m0][kq], f0, f1);
+            put(&Ah[m1][kq], &Al[m1][kq], f2, f3);
+            *(uint4*)&Bh[m0][kq] = r4; *(uint4*)&Bh[m1][kq] = r5; *(uint4*)&Bl[m0][kq] = r6; *(uint4*)&Bl[m1][kq] = r7;
+        };
+        load(0);
+        store();
+        __syncthreads();
+        for (int k0 = 0; k0 < K; k0 += BK) {
+            const bool more = k0 + BK < K;
+            if (more) load(k0 + BK);                // into registers while this K-tile is multiplied
+#pragma unroll
+            for (int ks = 0; ks < BK; ks += 16) {
+                const int kk = ks + 8 * (lane >> 5);
+                v8bf ah[2], al[2], bh[2], bl[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    __builtin_memcpy(&ah[t], &Ah[wm + 32 * t + (lane & 31)][kk], 16);
+                    __builtin_memcpy(&al[t], &Al[wm + 32 * t + (lane & 31)][kk], 16);
+                    __builtin_memcpy(&bh[t], &Bh[wn + 32 * t + (lane & 31)][kk], 16);
+                    __builtin_memcpy(&bl[t], &Bl[wn + 32 * t + (lane & 31)][kk], 16);
+                }
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[a], bh[b], acc[a][b], 0, 0, 0);
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bl[b], acc[a][b], 0, 0, 0);
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bh[b], acc[a][b], 0, 0, 0);
+                    }
+            }
+            __syncthreads();                        // every read of this K-tile is done
+            if (more) {
+                store();
+                __syncthreads();
+            }
+        }
+        // columns ascend over tiles and b, so a strict comparison keeps the lowest
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int gc = col0 + wn + 32 * b + (lane & 31);
+            if (gc < N) {
+                const float bn = EPI == 1 ? bn2[gc] : 0.0f;
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const float v = EPI == 1 ? (s_an[wm + 32 * a + out_row(lane, r)] + bn) - 2.0f * acc[a][b][r]
+                                                 : -acc[a][b][r];
+                        const bool better = v < bv[a][r];
+                        bv[a][r] = better ? v : bv[a][r];
+                        bc[a][r] = better ? (col0 + wn + 32 * b) >> 5 : bc[a][r];
+                    }
+            }
+        }
+    }
+    // over the 32 lanes of a row, then the two waves of a row
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const unsigned u = __float_as_uint(bv[a][r]);
+            unsigned key = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+            unsigned col = (unsigned)(bc[a][r] * 32 + (lane & 31));
+            if (col >= (unsigned)N) key = 0xFFFFFFFFu;              // a lane without columns
+            for (int o = 16; o > 0; o >>= 1) {
+                const unsigned ok = __shfl_xor(key, o), oc = __shfl_xor(col, o);
+                const bool take = ok < key || (ok == key && oc < col);
+                key = take ? ok : key;
+                col = take ? oc : col;
+            }
+            if ((lane & 31) == 0)
+                atomicMin(&s_best[wm + 32 * a + out_row(lane, r)], ((unsigned long long)key << 32) | col);
+        }
+    __syncthreads();
+    if (tid < BM && row0 + tid < n) {
+        if (gridDim.y == 1) out[row0 + tid] = (int32_t)(unsigned)s_best[tid];
+        else atomicMin(&best[row0 + tid], s_best[tid]);
+    }
+}
+
+namespace {
+__global__ void fill_u64_kernel(unsigned long long* p, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = ~0ull;
+}
+__global__ void best_column_kernel(const unsigned long long* best, int64_t n, int32_t* out) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) out[i] = (int32_t)(unsigned)best[i];
+}
+// Workgroups that share a row tile: enough for about three rounds of the
+// resident ones (two per CU) where the rows alone do not give them.
+int assign_split(int64_t n, int64_t N) {
+    const int64_t rows = (n + BM - 1) / BM, tiles = (N + BN - 1) / BN;
+    return (int)std::min<int64_t>(tiles, std::max<int64_t>(1, 1536 / rows));
+}
+}  // namespace
+
+// scratch of launch_assign: the rows' (distance, column) slots when columns are split
+size_t assign_scratch_bytes(int64_t n, int64_t N)
+{
+    return assign_split(n, N) > 1 ? sizeof(unsigned long long) * (size_t)n : 0;
+}
+
+hipError_t launch_assign(const float* A, int64_t n, int K, const unsigned short* Bh, const unsigned short* Bl,
+                         int64_t N, const float* an2, const float* bn2, int neg_ip, int32_t* out, void* scratch,
+                         hipStream_t st)
+{
+    if (n <= 0) return hipSuccess;
+    unsigned long long* best = (unsigned long long*)scratch;
+    const int tiles = (int)((N + BN - 1) / BN), split = assign_split(n, N), per = (tiles + split - 1) / split;
+    const dim3 grid((unsigned)((n + BM - 1) / BM), (unsigned)((tiles + per - 1) / per));
+    const dim3 g1((unsigned)((n + 255) / 256));
+    if (grid.y > 1) hipLaunchKernelGGL(fill_u64_kernel, g1, dim3(256), 0, st, best, n);
+    if (neg_ip)
+        hipLaunchKernelGGL(assign_bf16x3_kernel<2>, grid, dim3(256), 0, st, A, n, K, Bh, Bl, (int)N, an2, bn2, per,
+                           best, out);
+    else
+        hipLaunchKernelGGL(assign_bf16x3_kernel<1>, grid, dim3(256), 0, st, A, n, K, Bh, Bl, (int)N, an2, bn2, per,
+                           best, out);
+    if (grid.y > 1) hipLaunchKernelGGL(best_column_kernel, g1, dim3(256), 0, st, best, n, out);
     return hipGetLastError();
 }
 

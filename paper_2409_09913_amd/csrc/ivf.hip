@@ -5,6 +5,8 @@
 //  * per-list means with FP64 sums in member order (the k-means update), so
 //    the same input gives the same centroids bit for bit on every run;
 //  * a row gather (the k-means initial centroids).
+// Nothing here waits for the host: the list offsets and the chunks of the
+// means are prefix sums on the device.
 #include <algorithm>
 
 #include "erq_common.h"
@@ -14,12 +16,13 @@ namespace erq {
 namespace {
 
 constexpr int kSortThreads = 256;
-constexpr int kSortMaxBlocks = 128;
+constexpr int kSortMaxBlocks = 512;
 constexpr int kMeanChunk = 1024;      // members per partial sum
 
 inline size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// blocks of the bucket sort: at most kSortMaxBlocks, and at most 16M per-block
+// blocks of the bucket sort: at most kSortMaxBlocks (two per CU: 200,000 rows
+// take 38 us of placement against 123 with 128), and at most 16M per-block
 // list counters in total
 int sort_blocks(int64_t n, int64_t nlist) {
     int64_t g = std::min<int64_t>(kSortMaxBlocks, std::max<int64_t>(1, ((int64_t)1 << 24) / std::max<int64_t>(nlist, 1)));
@@ -27,27 +30,80 @@ int sort_blocks(int64_t n, int64_t nlist) {
     return (int)g;
 }
 
-// cnt2[b][l] = rows of block b's contiguous chunk in list l
+// cnt2[b][l] = rows of block b's contiguous chunk in list l; bad (or null) is
+// set when an id lies outside [0, nlist) (such rows are not counted)
 __global__ __launch_bounds__(kSortThreads) void bucket_count_kernel(const int32_t* __restrict__ assign, int64_t n,
                                                                     int64_t nlist, int64_t chunk,
-                                                                    int32_t* __restrict__ cnt2)
+                                                                    int32_t* __restrict__ cnt2,
+                                                                    int32_t* __restrict__ bad)
 {
     const int64_t b = blockIdx.x;
     const int64_t r0 = b * chunk, r1 = min(n, r0 + chunk);
-    for (int64_t r = r0 + threadIdx.x; r < r1; r += kSortThreads) atomicAdd(&cnt2[b * nlist + assign[r]], 1);
+    for (int64_t r = r0 + threadIdx.x; r < r1; r += kSortThreads) {
+        const int32_t l = assign[r];
+        if (l < 0 || l >= nlist) {
+            if (bad) atomicOr(bad, 1);
+            continue;
+        }
+        atomicAdd(&cnt2[b * nlist + l], 1);
+    }
 }
 
-// per list: base2[b][l] = list_off[l] + rows of list l in blocks before b (in place over cnt2)
-__global__ void bucket_base_kernel(int32_t* __restrict__ cnt2, int64_t nlist, int G, const int64_t* __restrict__ list_off)
+// per list: exclusive prefix of cnt2 over the G blocks (in place) and the
+// total.  32 lists per workgroup; thread (list, eighth) sums its eighth of the
+// blocks, the eighths are combined in LDS
+__global__ __launch_bounds__(256) void bucket_total_kernel(int32_t* __restrict__ cnt2, int64_t nlist, int G,
+                                                           int32_t* __restrict__ cnt)
 {
-    const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ int32_t part[8][32];
+    const int lq = threadIdx.x & 31, e = threadIdx.x >> 5;
+    const int64_t l = (int64_t)blockIdx.x * 32 + lq;
+    const int per = (G + 7) / 8, b0 = min(G, e * per), b1 = min(G, b0 + per);
+    int32_t sum = 0;
+    if (l < nlist)
+#pragma unroll 8
+        for (int b = b0; b < b1; ++b) sum += cnt2[(int64_t)b * nlist + l];
+    part[e][lq] = sum;
+    __syncthreads();
     if (l >= nlist) return;
-    int64_t run = list_off[l];
-    for (int b = 0; b < G; ++b) {
+    int32_t run = 0;
+    for (int w = 0; w < e; ++w) run += part[w][lq];
+    if (e == 7) cnt[l] = run + sum;
+#pragma unroll 8
+    for (int b = b0; b < b1; ++b) {
         const int32_t c = cnt2[(int64_t)b * nlist + l];
-        cnt2[(int64_t)b * nlist + l] = (int32_t)run;
+        cnt2[(int64_t)b * nlist + l] = run;
         run += c;
     }
+}
+
+// One workgroup: list_off = exclusive prefix of the counts, chunk0 = exclusive
+// prefix of their chunks of kMeanChunk members (nlist + 1 of each).
+__global__ __launch_bounds__(1024) void list_prefix_kernel(const int32_t* __restrict__ cnt, int64_t nlist,
+                                                           int64_t* __restrict__ list_off,
+                                                           int32_t* __restrict__ chunk0)
+{
+    __shared__ long long s_n[16], s_c[16];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int64_t per = (nlist + 1023) / 1024, l0 = min(nlist, tid * per), l1 = min(nlist, l0 + per);
+    long long n = 0, c = 0;
+    for (int64_t l = l0; l < l1; ++l) { n += cnt[l]; c += (cnt[l] + kMeanChunk - 1) / kMeanChunk; }
+    long long in = n, ic = c;
+    for (int o = 1; o < 64; o <<= 1) {
+        const long long un = __shfl_up(in, o), uc = __shfl_up(ic, o);
+        if (lane >= o) { in += un; ic += uc; }
+    }
+    if (lane == 63) { s_n[wid] = in; s_c[wid] = ic; }
+    __syncthreads();
+    long long rn = in - n, rc = ic - c;
+    for (int w = 0; w < wid; ++w) { rn += s_n[w]; rc += s_c[w]; }
+    for (int64_t l = l0; l < l1; ++l) {
+        list_off[l] = rn;
+        chunk0[l] = (int32_t)rc;
+        rn += cnt[l];
+        rc += (cnt[l] + kMeanChunk - 1) / kMeanChunk;
+    }
+    if (tid == 1023) { list_off[nlist] = rn; chunk0[nlist] = (int32_t)rc; }
 }
 
 // Block b places the rows of its chunk in rounds of kSortThreads rows: a row's
@@ -57,6 +113,7 @@ __global__ void bucket_base_kernel(int32_t* __restrict__ cnt2, int64_t nlist, in
 // ordered by barriers, so positions ascend with the row number.
 __global__ __launch_bounds__(kSortThreads) void bucket_place_kernel(const int32_t* __restrict__ assign, int64_t n,
                                                                     int64_t nlist, int64_t chunk,
+                                                                    const int64_t* __restrict__ list_off,
                                                                     int32_t* __restrict__ base2,
                                                                     int32_t* __restrict__ ids32)
 {
@@ -78,7 +135,7 @@ __global__ __launch_bounds__(kSortThreads) void bucket_place_kernel(const int32_
                     ++cnt;
                 }
             }
-            if (first == t) s_base[t] = atomicAdd(&base2[b * nlist + l], cnt);
+            if (first == t) s_base[t] = (int32_t)list_off[l] + atomicAdd(&base2[b * nlist + l], cnt);
         }
         __syncthreads();
         if (l >= 0) ids32[s_base[first] + rank] = (int32_t)r;
@@ -87,35 +144,45 @@ __global__ __launch_bounds__(kSortThreads) void bucket_place_kernel(const int32_
 }
 
 // partial FP64 sums of one (list, chunk of kMeanChunk members): thread t sums
-// dimensions t, t + 256, ... over the chunk's members in order
+// dimensions 4t .. 4t+3 (then those blockDim further) over the chunk's members
+// in order, with the 16-byte loads of eight members in flight.  The grid is an
+// upper bound of the number of chunks.
 __global__ __launch_bounds__(256) void list_psum_kernel(const float* __restrict__ x, int dp,
                                                         const int32_t* __restrict__ ids32,
-                                                        const int64_t* __restrict__ list_off,
-                                                        const int32_t* __restrict__ chunk_list,
-                                                        const int32_t* __restrict__ chunk_first,
+                                                        const int64_t* __restrict__ list_off, int64_t nlist,
+                                                        const int32_t* __restrict__ chunk0,
                                                         double* __restrict__ psum)
 {
     const int64_t c = blockIdx.x;
-    const int l = chunk_list[c];
-    const int64_t m0 = list_off[l] + (int64_t)chunk_first[c] * kMeanChunk;
-    const int64_t m1 = min(list_off[l + 1], m0 + kMeanChunk);
-    for (int d = threadIdx.x; d < dp; d += 256) {
-        double acc = 0.0;
+    if (c >= chunk0[nlist]) return;
+    int64_t lo = 0, hi = nlist;                    // last list with chunk0[l] <= c: the one that holds c
+    while (hi - lo > 1) { const int64_t mid = (lo + hi) >> 1; if (chunk0[mid] <= c) lo = mid; else hi = mid; }
+    const int64_t m0 = list_off[lo] + (c - chunk0[lo]) * kMeanChunk;
+    const int64_t m1 = min(list_off[lo + 1], m0 + kMeanChunk);
+    for (int d = 4 * threadIdx.x; d < dp; d += 4 * blockDim.x) {
+        double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
 #pragma unroll 8
-        for (int64_t v = m0; v < m1; ++v) acc += (double)x[(int64_t)ids32[v] * dp + d];
-        psum[c * dp + d] = acc;
+        for (int64_t v = m0; v < m1; ++v) {
+            const float4 t = *(const float4*)(x + (int64_t)ids32[v] * dp + d);
+            a0 += (double)t.x;
+            a1 += (double)t.y;
+            a2 += (double)t.z;
+            a3 += (double)t.w;
+        }
+        double* o = psum + c * dp + d;
+        o[0] = a0; o[1] = a1; o[2] = a2; o[3] = a3;
     }
 }
 
 // mean of list l from its chunks' partial sums in chunk order; an empty list keeps its centroid
 __global__ __launch_bounds__(256) void list_mean_kernel(const double* __restrict__ psum, int dp,
                                                         const int64_t* __restrict__ list_off,
-                                                        const int32_t* __restrict__ list_chunk0, float* __restrict__ cent)
+                                                        const int32_t* __restrict__ chunk0, float* __restrict__ cent)
 {
     const int l = blockIdx.x;
     const int64_t cnt = list_off[l + 1] - list_off[l];
     if (cnt == 0) return;
-    const int c0 = list_chunk0[l], c1 = list_chunk0[l + 1];
+    const int c0 = chunk0[l], c1 = chunk0[l + 1];
     for (int d = threadIdx.x; d < dp; d += 256) {
         double s = 0.0;
         for (int c = c0; c < c1; ++c) s += psum[(int64_t)c * dp + d];
@@ -139,68 +206,56 @@ size_t bucket_scratch_bytes(int64_t n, int64_t nlist)
     return a256(sizeof(int32_t) * (size_t)sort_blocks(n, nlist) * (size_t)nlist);
 }
 
-hipError_t launch_bucket_sort(const int32_t* assign, int64_t n, int64_t nlist, const int64_t* list_off,
-                              int32_t* ids32, void* scratch, hipStream_t st)
+hipError_t launch_bucket_count(const int32_t* assign, int64_t n, int64_t nlist, int32_t* cnt, int32_t* bad,
+                               void* scratch, hipStream_t st)
 {
-    if (n <= 0) return hipSuccess;
     const int G = sort_blocks(n, nlist);
     const int64_t chunk = (n + G - 1) / G;
     int32_t* cnt2 = (int32_t*)scratch;
     hipError_t e = hipMemsetAsync(cnt2, 0, sizeof(int32_t) * (size_t)G * nlist, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(bucket_count_kernel, dim3(G), dim3(kSortThreads), 0, st, assign, n, nlist, chunk, cnt2);
-    hipLaunchKernelGGL(bucket_base_kernel, dim3((unsigned)((nlist + 255) / 256)), dim3(256), 0, st, cnt2, nlist, G,
-                       list_off);
-    hipLaunchKernelGGL(bucket_place_kernel, dim3(G), dim3(kSortThreads), 0, st, assign, n, nlist, chunk, cnt2, ids32);
+    if (n > 0)
+        hipLaunchKernelGGL(bucket_count_kernel, dim3(G), dim3(kSortThreads), 0, st, assign, n, nlist, chunk, cnt2, bad);
+    hipLaunchKernelGGL(bucket_total_kernel, dim3((unsigned)((nlist + 31) / 32)), dim3(256), 0, st, cnt2, nlist, G, cnt);
     return hipGetLastError();
 }
 
-// chunk tables: chunk -> (list, index within the list), list -> first chunk
-static void mean_chunks(const std::vector<int64_t>& off, std::vector<int32_t>& clist, std::vector<int32_t>& cfirst,
-                        std::vector<int32_t>& l0)
+hipError_t launch_bucket_place(const int32_t* assign, int64_t n, int64_t nlist, const int64_t* list_off,
+                               int32_t* ids32, void* scratch, hipStream_t st)
 {
-    const int64_t C = (int64_t)off.size() - 1;
-    l0.assign(C + 1, 0);
-    clist.clear();
-    cfirst.clear();
-    for (int64_t l = 0; l < C; ++l) {
-        l0[l] = (int32_t)clist.size();
-        const int64_t nc = (off[l + 1] - off[l] + kMeanChunk - 1) / kMeanChunk;
-        for (int64_t c = 0; c < nc; ++c) { clist.push_back((int32_t)l); cfirst.push_back((int32_t)c); }
-    }
-    l0[C] = (int32_t)clist.size();
+    if (n <= 0) return hipSuccess;
+    const int G = sort_blocks(n, nlist);
+    const int64_t chunk = (n + G - 1) / G;
+    hipLaunchKernelGGL(bucket_place_kernel, dim3(G), dim3(kSortThreads), 0, st, assign, n, nlist, chunk, list_off,
+                       (int32_t*)scratch, ids32);
+    return hipGetLastError();
 }
 
-size_t list_mean_scratch_bytes(const std::vector<int64_t>& off, int dp)
+hipError_t launch_list_prefix(const int32_t* cnt, int64_t nlist, int64_t* list_off, int32_t* chunk0, hipStream_t st)
 {
-    std::vector<int32_t> cl, cf, l0;
-    mean_chunks(off, cl, cf, l0);
-    return a256(sizeof(double) * std::max<size_t>(cl.size(), 1) * dp) + 2 * a256(sizeof(int32_t) * std::max<size_t>(cl.size(), 1)) +
-           a256(sizeof(int32_t) * l0.size());
+    hipLaunchKernelGGL(list_prefix_kernel, dim3(1), dim3(1024), 0, st, cnt, nlist, list_off, chunk0);
+    return hipGetLastError();
 }
 
-hipError_t launch_list_mean(const float* x, int dp, const int32_t* ids32, const std::vector<int64_t>& off,
-                            const int64_t* list_off, float* cent, void* scratch, hipStream_t st)
+// chunks of all lists: at most one per list beside the full ones
+static int64_t mean_chunks(int64_t n, int64_t nlist) { return n / kMeanChunk + std::min(n, nlist); }
+
+size_t list_mean_scratch_bytes(int64_t n, int64_t nlist, int dp)
 {
-    std::vector<int32_t> cl, cf, l0;
-    mean_chunks(off, cl, cf, l0);
-    const size_t nc = cl.size();
-    char* w = (char*)scratch;
-    double* psum = (double*)w; w += a256(sizeof(double) * std::max<size_t>(nc, 1) * dp);
-    int32_t* d_cl = (int32_t*)w; w += a256(sizeof(int32_t) * std::max<size_t>(nc, 1));
-    int32_t* d_cf = (int32_t*)w; w += a256(sizeof(int32_t) * std::max<size_t>(nc, 1));
-    int32_t* d_l0 = (int32_t*)w;
-    hipError_t e = hipSuccess;
-    if (nc) e = hipMemcpyAsync(d_cl, cl.data(), sizeof(int32_t) * nc, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess && nc) e = hipMemcpyAsync(d_cf, cf.data(), sizeof(int32_t) * nc, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(d_l0, l0.data(), sizeof(int32_t) * l0.size(), hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) return e;
-    if (nc) hipLaunchKernelGGL(list_psum_kernel, dim3((unsigned)nc), dim3(256), 0, st, x, dp, ids32, list_off, d_cl, d_cf, psum);
-    const int64_t C = (int64_t)off.size() - 1;
-    hipLaunchKernelGGL(list_mean_kernel, dim3((unsigned)C), dim3(256), 0, st, psum, dp, list_off, d_l0, cent);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(st);      // the host chunk tables go out of scope
-    return e;
+    return a256(sizeof(double) * (size_t)std::max<int64_t>(mean_chunks(n, nlist), 1) * dp);
+}
+
+hipError_t launch_list_mean(const float* x, int64_t n, int dp, const int32_t* ids32, const int64_t* list_off,
+                            int64_t nlist, const int32_t* chunk0, float* cent, void* scratch, hipStream_t st)
+{
+    double* psum = (double*)scratch;
+    const int64_t nc = mean_chunks(n, nlist);
+    const int th = std::min(256, (dp / 4 + 63) / 64 * 64);
+    if (nc > 0)
+        hipLaunchKernelGGL(list_psum_kernel, dim3((unsigned)nc), dim3(th), 0, st, x, dp, ids32, list_off, nlist, chunk0,
+                           psum);
+    hipLaunchKernelGGL(list_mean_kernel, dim3((unsigned)nlist), dim3(256), 0, st, psum, dp, list_off, chunk0, cent);
+    return hipGetLastError();
 }
 
 hipError_t launch_gather_rows(const float* x, int dp, const int64_t* rows, int64_t m, float* out, hipStream_t st)

@@ -1,10 +1,9 @@
 // Selection and list building:
 //  * row_topk: the k smallest entries of each row of a distance matrix,
 //    ascending by (value, column) -- the nprobe nearest centroids of the IVF
-//    probe (Sec. 4.1) and the nearest centroid of a k-means assignment.
+//    probe (Sec. 4.1).
 //    Exact radix select on the order-preserving integer image of the floats
 //    (4 passes of 8 bits), then a stable compaction and a bitonic sort.
-//  * IVF list construction: the member count of every list.
 //  * residuals r = x - c and ||r||^2 (FP64 accumulate) in list order.
 #include "erq_common.h"
 
@@ -179,16 +178,6 @@ __global__ __launch_bounds__(kSelThreads) void row_topk_kernel(
 }
 
 // ---- list construction ---------------------------------------------------
-__global__ void count_kernel(const int32_t* __restrict__ assign, int64_t n, int64_t nlist, int32_t* __restrict__ cnt,
-                             int32_t* __restrict__ bad)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    int32_t l = assign[i];
-    if (l < 0 || l >= nlist) { atomicOr(bad, 1); return; }
-    atomicAdd(&cnt[l], 1);
-}
-
 // residual rows in list order: res[v] = x[ids[v]] - cent[assign[ids[v]]]; norm2 in FP64
 __global__ void residual_kernel(const float* __restrict__ x, const int64_t* __restrict__ ids,
                                 const int32_t* __restrict__ assign, const float* __restrict__ cent,
@@ -223,13 +212,6 @@ hipError_t launch_row_topk(const float* D, int64_t n, int64_t N, int k, int32_t*
     else if (N <= 16 * kSelThreads) hipLaunchKernelGGL(row_topk_kernel<16>, g, b, 0, st, D, N, k, idx, val);
     else if (N <= 32 * kSelThreads) hipLaunchKernelGGL(row_topk_kernel<32>, g, b, 0, st, D, N, k, idx, val);
     else hipLaunchKernelGGL(row_topk_kernel<0>, g, b, 0, st, D, N, k, idx, val);
-    return hipGetLastError();
-}
-
-hipError_t launch_count(const int32_t* assign, int64_t n, int64_t nlist, int32_t* cnt, int32_t* bad, hipStream_t st)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(count_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, assign, n, nlist, cnt, bad);
     return hipGetLastError();
 }
 
