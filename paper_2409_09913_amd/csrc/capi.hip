@@ -13,25 +13,21 @@
 namespace erq {
 
 // launchers defined in the other translation units
-hipError_t launch_split_bf16(const float* x, int64_t n, unsigned short* hi, unsigned short* lo, hipStream_t st);
-hipError_t launch_split_norm(const float* X, int64_t n, int K, unsigned short* hi, unsigned short* lo, float* n2,
-                             hipStream_t st);
-hipError_t launch_split_bf16_t(const float* x, int K, int N, unsigned short* hi, unsigned short* lo, hipStream_t st);
-hipError_t launch_gemm_bf16x3(const unsigned short* Ah, const unsigned short* Al, int64_t n,
-                              const unsigned short* Bh, const unsigned short* Bl, int64_t N, int K,
+size_t plane_elems(int64_t n, int K);
+hipError_t launch_split_norm(const float* X, int64_t n, int K, unsigned short* planes, float* n2, hipStream_t st);
+hipError_t launch_split_t(const float* x, int K, int N, unsigned short* planes, hipStream_t st);
+hipError_t launch_gemm_bf16x3(const unsigned short* A, int64_t n, const unsigned short* B, int64_t N, int K,
                               float* out, int64_t ldo, hipStream_t st);
-hipError_t launch_sqdist_pre(const unsigned short* Ah, const unsigned short* Al, int64_t n,
-                             const unsigned short* Bh, const unsigned short* Bl, int64_t N, int K,
-                             const float* an2, const float* bn2, float* out, hipStream_t st, int neg_ip);
+hipError_t launch_probe_products(const unsigned short* A, int64_t n, int K, const float* an2, const unsigned short* B,
+                                 int64_t N, const float* bn2, int neg_ip, float* D, const unsigned short* R, int NR,
+                                 float* rot, hipStream_t st);
 hipError_t launch_pack_n(const uint8_t* codes, const int64_t* list_off, const int64_t* tile_off,
                          int64_t nlist, int dp, int bits, int64_t ntiles, uint8_t* packed, hipStream_t st);
 hipError_t launch_unpack_n(const uint8_t* packed, const int64_t* list_off, const int64_t* tile_off,
                            int64_t nlist, int dp, int bits, int64_t ntiles, uint8_t* codes, hipStream_t st);
-hipError_t launch_norm(const float* X, int64_t n, int K, float* n2, hipStream_t st);
 size_t assign_scratch_bytes(int64_t n, int64_t N);
-hipError_t launch_assign(const float* A, int64_t n, int K, const unsigned short* Bh, const unsigned short* Bl,
-                         int64_t N, const float* an2, const float* bn2, int neg_ip, int32_t* out, void* scratch,
-                         hipStream_t st);
+hipError_t launch_assign(const float* A, int64_t n, int K, const unsigned short* B, int64_t N, const float* an2,
+                         const float* bn2, int neg_ip, int32_t* out, void* scratch, hipStream_t st);
 
 static thread_local std::string g_err;
 
@@ -94,8 +90,8 @@ void prof_end(int rec, hipStream_t st)
 void free_index_storage(Index* ix)
 {
     hipFree(ix->cent); hipFree(ix->cent_rot); hipFree(ix->list_off); hipFree(ix->tile_off);
-    hipFree(ix->cent_hi); hipFree(ix->cent_lo); hipFree(ix->cent_n2);
-    ix->cent_hi = ix->cent_lo = nullptr; ix->cent_n2 = nullptr;
+    hipFree(ix->cent_pl); hipFree(ix->cent_n2);
+    ix->cent_pl = nullptr; ix->cent_n2 = nullptr;
     hipFree(ix->list_order); hipFree(ix->ids); hipFree(ix->fac); hipFree(ix->sfac); hipFree(ix->codes);
     hipFree(ix->msb); hipFree(ix->fac1);
     ix->cent = ix->cent_rot = nullptr; ix->list_off = ix->tile_off = nullptr; ix->list_order = nullptr;
@@ -228,15 +224,14 @@ int set_list_meta(Index* ix, const std::vector<int64_t>& off, hipStream_t st) {
     return ERQ_OK;
 }
 
-// BF16 hi/lo planes and squared norms of the index's raw centroids (the
+// BF16 planes and squared norms of the index's raw centroids (the
 // probe's fixed operand), from ix->cent
 hipError_t alloc_cent_planes(Index* ix, hipStream_t st)
 {
     const int64_t C = ix->nlist, dp = ix->dp;
-    hipError_t e = hipMalloc(&ix->cent_hi, sizeof(unsigned short) * C * dp);
-    if (e == hipSuccess) e = hipMalloc(&ix->cent_lo, sizeof(unsigned short) * C * dp);
+    hipError_t e = hipMalloc(&ix->cent_pl, sizeof(unsigned short) * plane_elems(C, (int)dp));
     if (e == hipSuccess) e = hipMalloc(&ix->cent_n2, sizeof(float) * C);
-    if (e == hipSuccess) e = launch_split_norm(ix->cent, C, (int)dp, ix->cent_hi, ix->cent_lo, ix->cent_n2, st);
+    if (e == hipSuccess) e = launch_split_norm(ix->cent, C, (int)dp, ix->cent_pl, ix->cent_n2, st);
     return e;
 }
 
@@ -253,47 +248,33 @@ int set_projection_matrix(Index* ix, hipStream_t st)
     return ERQ_OK;
 }
 
-struct ProbePre {           // operands already split (and their norms), or null
-    const unsigned short *qh = nullptr, *ql = nullptr; const float* qn = nullptr;
-    const unsigned short *ch = nullptr, *cl = nullptr; const float* cn = nullptr;
-};
-int probe_impl(const float* q, int64_t nq, const float* cent, int64_t nlist, int dp, int nprobe,
-               int32_t* probes, float* pdist, void* ws, size_t ws_bytes, hipStream_t st,
-               const ProbePre& pre = ProbePre(), int metric = ERQ_METRIC_L2);
-
-// distances nq x nlist, norms, and the BF16 hi/lo planes of both operands
-size_t probe_ws(int64_t nq, int64_t nlist, int dp) {
-    return align256(sizeof(float) * nq * nlist) + align256(sizeof(float) * nq) + align256(sizeof(float) * nlist) +
-           2 * align256(sizeof(unsigned short) * nq * dp) + 2 * align256(sizeof(unsigned short) * nlist * dp);
+// The probe of a search, from the centroid planes and norms that the index
+// keeps: the distances and (with R) the rotation in one launch, then the
+// selection.  Scratch: the query planes and the distances (probe_scratch).
+size_t probe_scratch(int64_t nq, int64_t nlist, int dp) {
+    return align256(sizeof(unsigned short) * plane_elems(nq, dp)) + align256(sizeof(float) * nq * nlist);
 }
-
-// pre: the BF16 planes and norms of the queries and / or centroids when the
-// caller has them (else computed here).  metric L2: ascending squared
-// distances; inner product / cosine: ascending negated inner products.
-int probe_impl(const float* q, int64_t nq, const float* cent, int64_t nlist, int dp, int nprobe,
-               int32_t* probes, float* pdist, void* ws, size_t ws_bytes, hipStream_t st, const ProbePre& pre,
-               int metric)
+int probe_impl(const float* q, int64_t nq, float* qn, const unsigned short* cent_pl, const float* cent_n2,
+               int64_t nlist, int dp, int nprobe, int32_t* probes, float* pdist, const unsigned short* R, int dc,
+               float* rot, void* ws, hipStream_t st, int metric)
 {
-    if (ws_bytes < probe_ws(nq, nlist, dp)) return fail(ERQ_ENOMEM, "coarse probe: workspace too small");
-    char* w = (char*)ws;
-    float* D = (float*)w; w += align256(sizeof(float) * nq * nlist);
-    float* qn = (float*)w; w += align256(sizeof(float) * nq);
-    float* cn = (float*)w; w += align256(sizeof(float) * nlist);
-    unsigned short* qh = (unsigned short*)w; w += align256(sizeof(unsigned short) * nq * dp);
-    unsigned short* ql = (unsigned short*)w; w += align256(sizeof(unsigned short) * nq * dp);
-    unsigned short* ch = (unsigned short*)w; w += align256(sizeof(unsigned short) * nlist * dp);
-    unsigned short* cl = (unsigned short*)w;
-    int pr = prof_begin(PK_PROBE, st);
-    const unsigned short *uqh = qh, *uql = ql, *uch = ch, *ucl = cl;
-    const float *uqn = qn, *ucn = cn;
-    if (pre.qh && pre.ql && pre.qn) { uqh = pre.qh; uql = pre.ql; uqn = pre.qn; }
-    else ERQ_HIP(launch_split_norm(q, nq, dp, qh, ql, qn, st));
-    if (pre.ch && pre.cl && pre.cn) { uch = pre.ch; ucl = pre.cl; ucn = pre.cn; }
-    else ERQ_HIP(launch_split_norm(cent, nlist, dp, ch, cl, cn, st));
-    ERQ_HIP(launch_sqdist_pre(uqh, uql, nq, uch, ucl, nlist, dp, uqn, ucn, D, st, metric != ERQ_METRIC_L2));
+    unsigned short* qp = (unsigned short*)ws;
+    float* D = (float*)((char*)ws + align256(sizeof(unsigned short) * plane_elems(nq, dp)));
+    int pr = prof_begin(PK_ROTATE, st);
+    ERQ_HIP(launch_split_norm(q, nq, dp, qp, qn, st));
+    prof_end(pr, st);
+    pr = prof_begin(PK_PROBE, st);
+    ERQ_HIP(launch_probe_products(qp, nq, dp, qn, cent_pl, nlist, cent_n2, metric != ERQ_METRIC_L2, D, R, dc, rot, st));
     ERQ_HIP(launch_row_topk(D, nq, nlist, nprobe, probes, pdist, st));
     prof_end(pr, st);
     return ERQ_OK;
+}
+
+// workspace of erq_coarse_probe: distances, norms and the planes of both operands
+size_t probe_ws(int64_t nq, int64_t nlist, int dp) {
+    return align256(sizeof(float) * nq * nlist) + align256(sizeof(float) * nq) + align256(sizeof(float) * nlist) +
+           align256(sizeof(unsigned short) * plane_elems(nq, dp)) +
+           align256(sizeof(unsigned short) * plane_elems(nlist, dp));
 }
 
 // One device allocation cut into 256-byte aligned pieces: a first walk with no
@@ -334,7 +315,7 @@ int kmeans_impl(const float* x, int64_t n, int dp, int64_t C, int iters, uint64_
     int64_t *drows = nullptr, *doff = nullptr;
     int32_t *asg = asg_out, *ids32 = nullptr, *cnt = nullptr, *chunk0 = nullptr;
     float *xn = nullptr, *cn = nullptr;
-    unsigned short *ch = nullptr, *cl = nullptr;
+    unsigned short* cp = nullptr;
     char *bscr = nullptr, *mscr = nullptr, *ascr = nullptr;
     auto lay = [&](Carve& m) {
         m.take(&drows, C);
@@ -345,8 +326,7 @@ int kmeans_impl(const float* x, int64_t n, int dp, int64_t C, int iters, uint64_
         m.take(&chunk0, C + 1);
         m.take(&xn, n);
         m.take(&cn, C);
-        m.take(&ch, (size_t)C * dp);
-        m.take(&cl, (size_t)C * dp);
+        m.take(&cp, plane_elems(C, dp));
         m.take(&bscr, bucket_scratch_bytes(n, C));
         m.take(&mscr, list_mean_scratch_bytes(n, C, dp));
         m.take(&ascr, assign_scratch_bytes(n, C));
@@ -358,10 +338,10 @@ int kmeans_impl(const float* x, int64_t n, int dp, int64_t C, int iters, uint64_
     lay(mem);
     ERQ_HIP(hipMemcpyAsync(drows, rows.data(), sizeof(int64_t) * C, hipMemcpyHostToDevice, st));
     ERQ_HIP(launch_gather_rows(x, dp, drows, C, cent, st));
-    ERQ_HIP(launch_norm(x, n, dp, xn, st));
+    ERQ_HIP(launch_split_norm(x, n, dp, nullptr, xn, st));
     for (int it = 0; it <= iters; ++it) {
-        ERQ_HIP(launch_split_norm(cent, C, dp, ch, cl, cn, st));
-        ERQ_HIP(launch_assign(x, n, dp, ch, cl, C, xn, cn, 0, asg, ascr, st));
+        ERQ_HIP(launch_split_norm(cent, C, dp, cp, cn, st));
+        ERQ_HIP(launch_assign(x, n, dp, cp, C, xn, cn, 0, asg, ascr, st));
         if (it == iters) break;
         ERQ_HIP(launch_bucket_count(asg, n, C, cnt, nullptr, bscr, st));
         ERQ_HIP(launch_list_prefix(cnt, C, doff, chunk0, st));
@@ -444,19 +424,16 @@ int erq_rotate(const float* x, int64_t n, int32_t dp, const float* P, int32_t pr
     if (x == out) return fail(ERQ_EINVAL, "erq_rotate: out must not alias x");
     hipStream_t st = (hipStream_t)stream;
     if (precision == 2) {
-        // the search's rotation: BF16 hi/lo planes of x and of P^T, three products per K chunk
+        // the search's rotation: BF16 planes of x and of P^T, three products per K chunk
         if (n == 0) return ERQ_OK;
-        struct Tmp { void* p[4] = {nullptr, nullptr, nullptr, nullptr}; ~Tmp() { for (void* q : p) hipFree(q); } } t;
-        ERQ_HIP(hipMalloc(&t.p[0], sizeof(unsigned short) * n * dp));
-        ERQ_HIP(hipMalloc(&t.p[1], sizeof(unsigned short) * n * dp));
-        ERQ_HIP(hipMalloc(&t.p[2], sizeof(unsigned short) * dp * dp));
-        ERQ_HIP(hipMalloc(&t.p[3], sizeof(unsigned short) * dp * dp));
-        auto* xh = (unsigned short*)t.p[0]; auto* xl = (unsigned short*)t.p[1];
-        auto* ph = (unsigned short*)t.p[2]; auto* pl = (unsigned short*)t.p[3];
+        struct Tmp { void* p[2] = {nullptr, nullptr}; ~Tmp() { for (void* q : p) hipFree(q); } } t;
+        ERQ_HIP(hipMalloc(&t.p[0], sizeof(unsigned short) * plane_elems(n, dp)));
+        ERQ_HIP(hipMalloc(&t.p[1], sizeof(unsigned short) * plane_elems(dp, dp)));
+        auto* xp = (unsigned short*)t.p[0]; auto* pp = (unsigned short*)t.p[1];
         int pr = prof_begin(PK_ROTATE, st);
-        ERQ_HIP(launch_split_bf16(x, n * dp, xh, xl, st));
-        ERQ_HIP(launch_split_bf16_t(P, dp, dp, ph, pl, st));
-        ERQ_HIP(launch_gemm_bf16x3(xh, xl, n, ph, pl, dp, dp, out, dp, st));
+        ERQ_HIP(launch_split_norm(x, n, dp, xp, nullptr, st));
+        ERQ_HIP(launch_split_t(P, dp, dp, pp, st));
+        ERQ_HIP(launch_gemm_bf16x3(xp, n, pp, dp, dp, out, dp, st));
         prof_end(pr, st);
         ERQ_HIP(hipStreamSynchronize(st));          // before the scratch planes are freed
         return ERQ_OK;
@@ -497,8 +474,15 @@ int erq_coarse_probe(const float* q, int64_t nq, const float* centroids, int64_t
     if (nq < 0 || nlist < 1 || nlist > (1LL << 31) - 1) return fail(ERQ_EINVAL, "erq_coarse_probe: bad sizes");
     if (nprobe < 1 || nprobe > 1024 || nprobe > nlist) return fail(ERQ_EUNSUPPORTED, "erq_coarse_probe: nprobe must be in [1, min(nlist, 1024)]");
     if (nq > 0 && (!q || !centroids || !probes || !workspace)) return fail(ERQ_EINVAL, "erq_coarse_probe: null pointer");
-    return probe_impl(q, nq, centroids, nlist, dp, nprobe, probes, pdist, workspace, ws_bytes, (hipStream_t)stream,
-                      ProbePre(), metric);
+    if (ws_bytes < probe_ws(nq, nlist, dp)) return fail(ERQ_ENOMEM, "coarse probe: workspace too small");
+    if (nq == 0) return ERQ_OK;
+    char* w = (char*)workspace;
+    float* qn = (float*)w; w += align256(sizeof(float) * nq);
+    float* cn = (float*)w; w += align256(sizeof(float) * nlist);
+    unsigned short* cp = (unsigned short*)w; w += align256(sizeof(unsigned short) * plane_elems(nlist, dp));
+    ERQ_HIP(launch_split_norm(centroids, nlist, dp, cp, cn, (hipStream_t)stream));
+    return probe_impl(q, nq, qn, cp, cn, nlist, dp, nprobe, probes, pdist, nullptr, 0, nullptr, w, (hipStream_t)stream,
+                      metric);
 }
 
 int erq_sample_rotation(int32_t dp, uint64_t seed, float* P_host)
@@ -531,12 +515,11 @@ int erq_index_create(int32_t dp, int32_t bits, int64_t nlist, const float* P, ui
     hipError_t e = P ? hipMemcpyAsync(ix->P, P, sizeof(float) * dp * dp, hipMemcpyDeviceToDevice, (hipStream_t)stream)
                      : hipMemcpyAsync(ix->P, hP.data(), sizeof(float) * dp * dp, hipMemcpyHostToDevice,
                                       (hipStream_t)stream);
-    if (e == hipSuccess) e = hipMalloc(&ix->pt_hi, sizeof(unsigned short) * dp * dp);
-    if (e == hipSuccess) e = hipMalloc(&ix->pt_lo, sizeof(unsigned short) * dp * dp);
-    if (e == hipSuccess) e = launch_split_bf16_t(ix->P, dp, dp, ix->pt_hi, ix->pt_lo, (hipStream_t)stream);
+    if (e == hipSuccess) e = hipMalloc(&ix->pt_pl, sizeof(unsigned short) * plane_elems(dp, dp));
+    if (e == hipSuccess) e = launch_split_t(ix->P, dp, dp, ix->pt_pl, (hipStream_t)stream);
     if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
     if (e != hipSuccess) {
-        hipFree(ix->P); hipFree(ix->pt_hi); hipFree(ix->pt_lo); delete ix;
+        hipFree(ix->P); hipFree(ix->pt_pl); delete ix;
         return fail(ERQ_EDEVICE, std::string("erq_index_create: ") + hipGetErrorString(e));
     }
     *out = ix;
@@ -639,9 +622,8 @@ int erq_index_load(const char* path, void* stream, erq_index* out)
         if (a == 3) { std::fseek(f, (long)sz[3], SEEK_CUR); continue; }   // list offsets: already uploaded
         if (sz[a]) { if (int rc = file_to_dev(f, dst[a], sz[a], buf, st)) return rc; }
     }
-    ERQ_HIP(hipMalloc(&ix->pt_hi, sizeof(unsigned short) * dp * dp));
-    ERQ_HIP(hipMalloc(&ix->pt_lo, sizeof(unsigned short) * dp * dp));
-    ERQ_HIP(launch_split_bf16_t(ix->P, dp, dp, ix->pt_hi, ix->pt_lo, st));
+    ERQ_HIP(hipMalloc(&ix->pt_pl, sizeof(unsigned short) * plane_elems(dp, dp)));
+    ERQ_HIP(launch_split_t(ix->P, dp, dp, ix->pt_pl, st));
     if (int rc = set_projection_matrix(ix, st)) return rc;
     ERQ_HIP(alloc_cent_planes(ix, st));
     ERQ_HIP(hipStreamSynchronize(st));
@@ -730,8 +712,7 @@ int erq_index_destroy(erq_index ix)
     free_index_storage(ix);
     hipFree(ix->P);
     hipFree(ix->Pd);
-    hipFree(ix->pt_hi);
-    hipFree(ix->pt_lo);
+    hipFree(ix->pt_pl);
     hipFree(ix->raw);
     delete ix;
     return ERQ_OK;
@@ -890,9 +871,8 @@ int erq_index_build(erq_index ix, const float* x, int64_t n, const float* centro
         ERQ_HIP(hipMemcpyAsync(asg, assign, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, st));
     } else if (n > 0) {
         int pr = prof_begin(PK_PROBE, st);
-        ERQ_HIP(launch_norm(x, n, dp, xn, st));
-        ERQ_HIP(launch_assign(x, n, dp, ix->cent_hi, ix->cent_lo, C, xn, ix->cent_n2, ix->metric != ERQ_METRIC_L2, asg,
-                              as, st));
+        ERQ_HIP(launch_split_norm(x, n, dp, nullptr, xn, st));
+        ERQ_HIP(launch_assign(x, n, dp, ix->cent_pl, C, xn, ix->cent_n2, ix->metric != ERQ_METRIC_L2, asg, as, st));
         prof_end(pr, st);
     }
     hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, st, bad, 1, 0);
@@ -1040,6 +1020,8 @@ int erq_rerank(erq_index ix, const float* q, int64_t nq, const int64_t* cand, in
     return ERQ_OK;
 }
 
+// The workspace: what lives through the whole search, then a region that holds
+// the probe's planes and distances and afterwards the scan's arrays.
 static size_t search_ws(Index* ix, int64_t nq, int nprobe, int k, int rerank_k) {
     const int kk = rerank_k > 0 ? rerank_k : k;
     size_t b = 0;
@@ -1048,12 +1030,18 @@ static size_t search_ws(Index* ix, int64_t nq, int nprobe, int k, int rerank_k) 
     b += align256(sizeof(float) * nq * nprobe);           // probe distances ||q - c||^2
     b += align256(sizeof(int64_t) * nq * kk);             // candidate ids
     b += align256(sizeof(float) * nq * kk);               // candidate estimates
-    b += 2 * align256(sizeof(unsigned short) * nq * ix->dp);   // BF16 hi/lo planes of the queries
     b += align256(sizeof(float) * nq);                          // ||q||^2
     b += 2 * align256(sizeof(int32_t) * nq);                    // per-query k and re-rank depth
     if (ix->metric == ERQ_METRIC_COSINE) b += align256(sizeof(float) * nq * ix->dp);   // unit-length queries
-    b += std::max(probe_ws(nq, ix->nlist, ix->dp), scan_workspace_bytes(nq, nprobe, ix->nlist, kk, ix->dc, ix->max_list));
-    return b;
+    const size_t scan = scan_workspace_bytes(nq, nprobe, ix->nlist, kk, ix->dc, ix->max_list);
+    // reported (and required) size: at least what row-major planes of both
+    // operands would take, so that the calls that fit a given workspace, the
+    // static scratch among them, stay the same
+    const size_t qp = 2 * align256(sizeof(unsigned short) * nq * ix->dp);
+    const size_t rows = align256(sizeof(float) * nq * ix->nlist) + align256(sizeof(float) * nq) +
+                        align256(sizeof(float) * ix->nlist) + qp +
+                        2 * align256(sizeof(unsigned short) * ix->nlist * ix->dp);
+    return std::max(b + qp + std::max(rows, scan), b + std::max(probe_scratch(nq, ix->nlist, ix->dp), scan));
 }
 
 int erq_search_workspace_size(erq_index ix, int64_t nq, int32_t nprobe, int32_t k, int32_t rerank_k, size_t* bytes)
@@ -1093,8 +1081,6 @@ static int search_run(Index* ix, const float* q, int64_t nq, int nprobe, int k, 
     float* pdist = (float*)w; w += align256(sizeof(float) * nq * nprobe);
     int64_t* cid = (int64_t*)w; w += align256(sizeof(int64_t) * nq * kk);
     float* cest = (float*)w; w += align256(sizeof(float) * nq * kk);
-    unsigned short* qh = (unsigned short*)w; w += align256(sizeof(unsigned short) * nq * ix->dp);
-    unsigned short* ql = (unsigned short*)w; w += align256(sizeof(unsigned short) * nq * ix->dp);
     float* qn = (float*)w; w += align256(sizeof(float) * nq);
     int32_t* kq = (int32_t*)w; w += align256(sizeof(int32_t) * nq);
     int32_t* rq = (int32_t*)w; w += align256(sizeof(int32_t) * nq);
@@ -1104,19 +1090,13 @@ static int search_run(Index* ix, const float* q, int64_t nq, int nprobe, int k, 
         q = qn_rows;
     }
     size_t rest = ws_bytes - (size_t)(w - (char*)workspace);
-    // q' = q P on the BF16 matrix cores from hi/lo planes (the probe's
-    // products and error bound); the planes serve the probe too
-    int pr = prof_begin(PK_ROTATE, st);
-    ERQ_HIP(launch_split_norm(q, nq, ix->dp, qh, ql, qn, st));
-    // (with the projection, the first dc coordinates of q' only)
-    ERQ_HIP(launch_gemm_bf16x3(qh, ql, nq, ix->pt_hi, ix->pt_lo, ix->dc, ix->dp, qrot, ix->dc, st));
-    prof_end(pr, st);
-    // the probe's ||q - c||^2 = ||q' - c'||^2 (P orthogonal) is the scan's ||s||^2 (L2), its
-    // -<q, c> = -<q', c'> the scan's per-pair term (inner-product metrics)
-    ProbePre pre;
-    pre.qh = qh; pre.ql = ql; pre.qn = qn;
-    pre.ch = ix->cent_hi; pre.cl = ix->cent_lo; pre.cn = ix->cent_n2;
-    if (int rc = probe_impl(q, nq, ix->cent, ix->nlist, ix->dp, nprobe, probes, pdist, w, rest, st, pre, ix->metric))
+    // q' = q P on the BF16 matrix cores (with the projection its first dc
+    // coordinates only) and the probe's distances in one launch, from the same
+    // query planes.  The probe's ||q - c||^2 = ||q' - c'||^2 (P orthogonal) is the
+    // scan's ||s||^2 (L2), its -<q, c> = -<q', c'> the scan's per-pair term
+    // (inner-product metrics).
+    if (int rc = probe_impl(q, nq, qn, ix->cent_pl, ix->cent_n2, ix->nlist, ix->dp, nprobe, probes, pdist, ix->pt_pl,
+                            ix->dc, qrot, w, st, ix->metric))
         return rc;
     const bool per_query = nprobe_q || k_q || rerank_q;
     if (per_query) {

@@ -69,12 +69,11 @@ struct Index {
     uint64_t seed = 0;             // seed P was sampled from (0 when the caller gave P)
     float* P = nullptr;            // dp x dp
     float* Pd = nullptr;           // dp x dc, the first dc columns of P (only when dc < dp)
-    unsigned short* pt_hi = nullptr;   // BF16 hi/lo planes of P^T (dp x dp each): the search's rotation
-    unsigned short* pt_lo = nullptr;
+    unsigned short* pt_pl = nullptr;   // BF16 planes of P^T: the search's rotation
     float* cent = nullptr;         // nlist x dp raw centroids
     float* cent_rot = nullptr;     // nlist x dp rotated centroids
-    unsigned short* cent_hi = nullptr;   // BF16 hi/lo planes of the raw centroids and their squared
-    unsigned short* cent_lo = nullptr;   // norms: the probe's B operand, fixed per index
+    unsigned short* cent_pl = nullptr; // BF16 planes of the raw centroids and their squared norms: the
+                                       // probe's B operand, fixed per index
     float* cent_n2 = nullptr;
     int64_t* list_off = nullptr;   // nlist + 1 (device)
     int64_t* tile_off = nullptr;   // nlist + 1, offset of each list's first tile (device)

@@ -1,11 +1,12 @@
-// Dense FP32 / BF16 matrix-core GEMM for the rotation by P (Sec. 3.4: the
-// data and the queries are multiplied by P^{-1} = P^T) and for the squared
-// distances of the coarse IVF probe (Sec. 4.1).
+// Matrix-core products: the rotation by P (Sec. 3.4: the data and the queries
+// are multiplied by P^{-1} = P^T) in FP32, BF16 or BF16 hi/lo form, the
+// distances of the coarse IVF probe (Sec. 4.1) and the assignment of rows to
+// centroids in the hi/lo form.
 //
-// Workgroup tile 128 x 128, 4 waves each owning 64 x 64 = 2 x 2 tiles of the
-// 32 x 32 MFMA.  FP32: v_mfma_f32_32x32x2_f32, K staged 16 at a time.
-// BF16: v_mfma_f32_32x32x16_bf16 with FP32 accumulation, K staged 32 at a
-// time, inputs rounded to BF16 (nearest even) while staging.
+// FP32 and BF16 (gemm_*): workgroup tile 128 x 128, 4 waves each owning 64 x 64
+// = 2 x 2 tiles of the 32 x 32 MFMA.  FP32: v_mfma_f32_32x32x2_f32, K staged 16
+// at a time.  BF16: v_mfma_f32_32x32x16_bf16 with FP32 accumulation, K staged
+// 32 at a time, inputs rounded to BF16 (nearest even) while staging.
 #include <algorithm>
 
 #include "erq_common.h"
@@ -27,11 +28,9 @@ __device__ inline unsigned short f2bf(float f) {
     return (unsigned short)(r >> 16);
 }
 
-// EPI: 0 = store C; 1 = store ||a||^2 + ||b||^2 - 2 C
-template <int EPI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(
     const float* __restrict__ A, int64_t n, int K, const float* __restrict__ B, int N, int b_trans,
-    float* __restrict__ out, int64_t ldo, const float* __restrict__ an2, const float* __restrict__ bn2)
+    float* __restrict__ out, int64_t ldo)
 {
     constexpr int BK = 16;
     // two LDS buffers: the next K-tile is loaded into registers while the
@@ -111,9 +110,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(
             for (int r = 0; r < 16; ++r) {
                 const int64_t gr = row0 + wm + 32 * a + out_row(lane, r);
                 if (gr >= n) continue;
-                float v = acc[a][b][r];
-                if (EPI == 1) v = (an2[gr] + bn2[gc]) - 2.0f * v;
-                out[gr * ldo + gc] = v;
+                out[gr * ldo + gc] = acc[a][b][r];
             }
         }
 }
@@ -193,289 +190,517 @@ hipError_t launch_gemm(const float* A, int64_t n, int K, const float* B, int N, 
     if (precision == 1)
         hipLaunchKernelGGL(gemm_bf16_kernel, grid, dim3(256), 0, st, A, n, K, B, N, b_trans, out, ldo);
     else
-        hipLaunchKernelGGL(gemm_f32_kernel<0>, grid, dim3(256), 0, st, A, n, K, B, N, b_trans, out, ldo,
-                           (const float*)nullptr, (const float*)nullptr);
+        hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, st, A, n, K, B, N, b_trans, out, ldo);
     return hipGetLastError();
 }
 
-// dist = ||a||^2 + ||b||^2 - 2 a.b, with norms an2 (n) and bn2 (N) precomputed
-// FP32 -> two BF16 planes: hi = bf16(x) and lo = bf16(x - hi) (x - hi is
-// exact, so x = hi + lo to 2^-17 relative); bit patterns, 4 elements per
-// thread, n a multiple of 4.
-__global__ __launch_bounds__(256) void split_bf16_kernel(const float* __restrict__ x, int64_t n,
-                                                         unsigned short* __restrict__ hi,
-                                                         unsigned short* __restrict__ lo)
-{
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i >= n) return;
-    const float4 v = *(const float4*)(x + i);
-    const float xv[4] = {v.x, v.y, v.z, v.w};
-    unsigned h[4], l[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        h[c] = f2bf(xv[c]);
-        l[c] = f2bf(xv[c] - __uint_as_float(h[c] << 16));
-    }
-    *(uint2*)(hi + i) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-    *(uint2*)(lo + i) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
+// ---------------------------------------------------------------------------
+// BF16 hi/lo products.  An FP32 matrix of rows (queries, centroids, columns of
+// P) is split into hi = bf16(x) and lo = bf16(x - hi) (x - hi is exact, so x =
+// hi + lo to 2^-17 relative) and a.b is taken as lo.hi + hi.lo + hi.hi per
+// 16-wide K chunk with FP32 accumulation: each product is off by at most 2^-15
+// |a_i b_i| (the dropped lo.lo and the two split residuals), so a distance by
+// at most 2^-14 sum|a_i b_i| plus FP32 accumulation: a few units in the 5th
+// digit, enough to order centroids except near-ties.
+//
+// Plane layout ("fragments"): rows in tiles of 32, K in chunks of 16; a (tile,
+// chunk) holds the hi fragment and then the lo fragment, 1 KB each, lane L's 16
+// bytes being the 8 consecutive k = 16 chunk + 8 (L / 32) .. of row L % 32.
+// That is the operand of v_mfma_f32_32x32x16_bf16, so every kernel below loads
+// it with one coalesced 16-byte load per lane, straight to registers.  Rows are
+// padded to a whole tile; what the padding holds does not matter (it only
+// reaches rows and columns that are not stored).
+// ---------------------------------------------------------------------------
+size_t plane_elems(int64_t n, int K) { return (size_t)((n + 31) / 32 * 32) * (size_t)K * 2; }
+
+namespace {
+
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+
+// two floats -> packed hi and lo planes (round to nearest even)
+__device__ inline void split2(float x, float y, unsigned& hi, unsigned& lo) {
+    const v2bf h = __builtin_convertvector((v2f){x, y}, v2bf);
+    __builtin_memcpy(&hi, &h, 4);
+    const v2bf l = __builtin_convertvector((v2f){x - __uint_as_float(hi << 16), y - __uint_as_float(hi & 0xFFFF0000u)},
+                                           v2bf);
+    __builtin_memcpy(&lo, &l, 4);
 }
 
-__device__ inline uint4 ld16(const unsigned short* p, bool ok) {
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (ok) v = *(const uint4*)p;
-    return v;
+// element offset of the hi plane of (row, k); the lo plane's is 512 further
+__device__ inline int64_t plane_at(int64_t row, int k, int K) {
+    return ((row >> 5) * (K >> 4) + (k >> 4)) * 1024 + (((row & 31) + 32 * ((k >> 3) & 1)) << 3) + (k & 7);
 }
 
-// EPI 1: squared distances ||a||^2 + ||b||^2 - 2 a.b of the coarse probe;
-// EPI 2: negated inner products -a.b (the probe of the inner-product
-// metrics); EPI 0: a.b (the query rotation).  Products on the BF16 matrix cores, from
-// operands split beforehand into hi
-// and lo BF16 planes (split_bf16_kernel): a.b = lo.hi + hi.lo + hi.hi per
-// 16-wide K chunk, FP32 accumulation.  Each product is off by at most
-// 2^-15 |a_i b_i| (the dropped lo.lo and the two split residuals), so a
-// distance by at most 2^-14 sum|a_i b_i| plus FP32 accumulation: a few units
-// in the 5th digit, enough to order centroids except near-ties.  A is n x K,
-// B is N x K (row-major planes), K a multiple of 32.  Tile 128 x 128, K
-// staged 32 at a time in one LDS buffer (40 KB, so several blocks share a
-// CU); the next K-tile is loaded into registers while the current one is
-// multiplied.
-template <int EPI>
-__global__ __launch_bounds__(256, 3) void sqdist_bf16x3_kernel(
-    const unsigned short* __restrict__ Ahg, const unsigned short* __restrict__ Alg, int64_t n, int K,
-    const unsigned short* __restrict__ Bhg, const unsigned short* __restrict__ Blg, int N,
-    float* __restrict__ out, int64_t ldo, const float* __restrict__ an2, const float* __restrict__ bn2)
+}  // namespace
+
+// Rows of X (n x K, K a multiple of 64) -> their planes (when given) and
+// squared norms ||x||^2 (FP32, when given); a lane has 4 consecutive elements
+// of a row, 256 k a step.  RPW = 4: a workgroup takes 16 rows, 4 per wave, and
+// puts a step's fragments together in LDS, so that the planes are written in
+// runs of 256 bytes (the padding per chunk spreads the 16 chunks of a row over
+// the banks).  RPW = 1, for few rows: one row per wave, 8-byte pieces written
+// straight from registers (one row of 768: 2.5 us against 6.6; 10,000 rows: 25
+// us against 13).
+template <int RPW>
+__global__ __launch_bounds__(256) void split_norm_kernel(const float* __restrict__ X, int64_t n, int K,
+                                                         unsigned short* __restrict__ planes, float* __restrict__ n2)
 {
-    constexpr int BK = 32, LD = BK + 8;
-    __shared__ __align__(16) unsigned short Ah[BM][LD], Al[BM][LD], Bh[BN][LD], Bl[BN][LD];
+    constexpr int RB = 4 * RPW, CS = 64 * RB + 16;    // rows of the workgroup, bytes of a chunk in LDS
+    __shared__ __align__(16) char frag[RPW > 1 ? 16 * CS : 16];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int64_t row0 = (int64_t)blockIdx.y * BM;
-    const int col0 = blockIdx.x * BN;
-    const int wm = (wid >> 1) * 64, wn = (wid & 1) * 64;
-    v16f acc[2][2];
-    for (int a = 0; a < 2; ++a) for (int b = 0; b < 2; ++b) for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
-    // per K-tile and plane: 128 rows x 32 k = 512 chunks of 16 bytes; thread
-    // tid moves chunks tid and tid + 256 (row m = e/4, k offset 8*(e%4))
-    const int m0 = tid >> 2, m1 = m0 + 64, kq = (tid & 3) * 8;
-    const bool a0 = row0 + m0 < n, a1 = row0 + m1 < n, b0 = col0 + m0 < N, b1 = col0 + m1 < N;
-    const unsigned short* pa0h = Ahg + (row0 + m0) * K + kq;
-    const unsigned short* pa1h = Ahg + (row0 + m1) * K + kq;
-    const unsigned short* pa0l = Alg + (row0 + m0) * K + kq;
-    const unsigned short* pa1l = Alg + (row0 + m1) * K + kq;
-    const unsigned short* pb0h = Bhg + (int64_t)(col0 + m0) * K + kq;
-    const unsigned short* pb1h = Bhg + (int64_t)(col0 + m1) * K + kq;
-    const unsigned short* pb0l = Blg + (int64_t)(col0 + m0) * K + kq;
-    const unsigned short* pb1l = Blg + (int64_t)(col0 + m1) * K + kq;
-    uint4 r0 = ld16(pa0h, a0), r1 = ld16(pa1h, a1), r2 = ld16(pa0l, a0), r3 = ld16(pa1l, a1);
-    uint4 r4 = ld16(pb0h, b0), r5 = ld16(pb1h, b1), r6 = ld16(pb0l, b0), r7 = ld16(pb1l, b1);
-    *(uint4*)&Ah[m0][kq] = r0; *(uint4*)&Ah[m1][kq] = r1; *(uint4*)&Al[m0][kq] = r2; *(uint4*)&Al[m1][kq] = r3;
-    *(uint4*)&Bh[m0][kq] = r4; *(uint4*)&Bh[m1][kq] = r5; *(uint4*)&Bl[m0][kq] = r6; *(uint4*)&Bl[m1][kq] = r7;
-    __syncthreads();
-    for (int k0 = 0; k0 < K; k0 += BK) {
-        const bool more = k0 + BK < K;
-        if (more) {                                 // next K-tile into registers while this one is multiplied
-            const int k1 = k0 + BK;
-            r0 = ld16(pa0h + k1, a0); r1 = ld16(pa1h + k1, a1); r2 = ld16(pa0l + k1, a0); r3 = ld16(pa1l + k1, a1);
-            r4 = ld16(pb0h + k1, b0); r5 = ld16(pb1h + k1, b1); r6 = ld16(pb0l + k1, b0); r7 = ld16(pb1l + k1, b1);
-        }
+    const int64_t rb = (int64_t)blockIdx.x * RB, r0 = rb + wid * RPW;
+    float s[RPW];
 #pragma unroll
-        for (int ks = 0; ks < BK; ks += 16) {
-            const int kk = ks + 8 * (lane >> 5);
-            v8bf ah[2], al[2], bh[2], bl[2];
+    for (int u = 0; u < RPW; ++u) s[u] = 0.0f;
+    for (int k0 = 0; k0 < K; k0 += 256) {
+        const int k = k0 + 4 * lane, nch = min(16, (K - k0) >> 4);
+        float4 v[RPW];
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                __builtin_memcpy(&ah[t], &Ah[wm + 32 * t + (lane & 31)][kk], 16);
-                __builtin_memcpy(&al[t], &Al[wm + 32 * t + (lane & 31)][kk], 16);
-                __builtin_memcpy(&bh[t], &Bh[wn + 32 * t + (lane & 31)][kk], 16);
-                __builtin_memcpy(&bl[t], &Bl[wn + 32 * t + (lane & 31)][kk], 16);
+        for (int u = 0; u < RPW; ++u)
+            v[u] = r0 + u < n && k < K ? *(const float4*)(X + (r0 + u) * K + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int u = 0; u < RPW; ++u) {
+            if (k < K) {
+                s[u] += v[u].x * v[u].x;
+                s[u] += v[u].y * v[u].y;
+                s[u] += v[u].z * v[u].z;
+                s[u] += v[u].w * v[u].w;
             }
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[a], bh[b], acc[a][b], 0, 0, 0);
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bl[b], acc[a][b], 0, 0, 0);
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bh[b], acc[a][b], 0, 0, 0);
+            if (planes) {
+                uint2 h, l;
+                split2(v[u].x, v[u].y, h.x, l.x);
+                split2(v[u].z, v[u].w, h.y, l.y);
+                if constexpr (RPW > 1) {              // chunk: hi | lo, each half 0 | half 1 of RB rows
+                    char* p = frag + (lane >> 2) * CS + (wid * RPW + u + RB * ((lane >> 1) & 1)) * 16 + 8 * (lane & 1);
+                    *(uint2*)p = h;
+                    *(uint2*)(p + 32 * RB) = l;
+                } else if (r0 < n && k < K) {
+                    unsigned short* p = planes + plane_at(r0, k, K);
+                    *(uint2*)p = h;
+                    *(uint2*)(p + 512) = l;
                 }
+            }
         }
-        __syncthreads();                        // every read of this K-tile is done
-        if (more) {
-            *(uint4*)&Ah[m0][kq] = r0; *(uint4*)&Ah[m1][kq] = r1; *(uint4*)&Al[m0][kq] = r2; *(uint4*)&Al[m1][kq] = r3;
-            *(uint4*)&Bh[m0][kq] = r4; *(uint4*)&Bh[m1][kq] = r5; *(uint4*)&Bl[m0][kq] = r6; *(uint4*)&Bl[m1][kq] = r7;
+        if (RPW > 1 && planes) {
+            __syncthreads();
+            uint4* o = (uint4*)planes + ((rb >> 5) * (K >> 4) + (k0 >> 4)) * 128 + (rb & 31);
+            for (int t = tid; t < nch * 4 * RB; t += 256) {
+                const int c = t / (4 * RB), i = t % (4 * RB);             // i: (plane, half) x row
+                o[c * 128 + (i / RB) * 32 + i % RB] = *(const uint4*)(frag + c * CS + i * 16);
+            }
             __syncthreads();
         }
     }
-    for (int a = 0; a < 2; ++a)
-        for (int b = 0; b < 2; ++b) {
-            const int gc = col0 + wn + 32 * b + (lane & 31);
-            if (gc >= N) continue;
-            for (int r = 0; r < 16; ++r) {
-                const int64_t gr = row0 + wm + 32 * a + out_row(lane, r);
-                if (gr >= n) continue;
-                if constexpr (EPI == 1) out[gr * ldo + gc] = (an2[gr] + bn2[gc]) - 2.0f * acc[a][b][r];
-                else if constexpr (EPI == 2) out[gr * ldo + gc] = -acc[a][b][r];
-                else out[gr * ldo + gc] = acc[a][b][r];
-            }
+    if (n2) {
+#pragma unroll
+        for (int u = 0; u < RPW; ++u) {
+            for (int o = 32; o > 0; o >>= 1) s[u] += __shfl_xor(s[u], o);
+            if (lane == 0 && r0 + u < n) n2[r0 + u] = s[u];
         }
+    }
 }
 
-// Transposed split of a K x N row-major matrix: hi/lo planes of its
-// transpose (N x K), for the B operand of sqdist_bf16x3_kernel.
-__global__ __launch_bounds__(256) void split_bf16_t_kernel(const float* __restrict__ x, int K, int N,
-                                                           unsigned short* __restrict__ hi,
-                                                           unsigned short* __restrict__ lo)
+hipError_t launch_split_norm(const float* X, int64_t n, int K, unsigned short* planes, float* n2, hipStream_t st)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;   // output index: row j of N, column k of K
-    if (i >= (int64_t)K * N) return;
-    const int64_t j = i / K, k = i - j * K;
-    const float v = x[k * N + j];
-    const unsigned h = f2bf(v);
-    hi[i] = (unsigned short)h;
-    lo[i] = f2bf(v - __uint_as_float(h << 16));
-}
-
-hipError_t launch_split_bf16_t(const float* x, int K, int N, unsigned short* hi, unsigned short* lo, hipStream_t st)
-{
-    const int64_t n = (int64_t)K * N;
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(split_bf16_t_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, x, K, N, hi, lo);
+    if (n <= 2048 || !planes)
+        hipLaunchKernelGGL(split_norm_kernel<1>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, X, n, K, planes, n2);
+    else
+        hipLaunchKernelGGL(split_norm_kernel<4>, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, st, X, n, K, planes, n2);
     return hipGetLastError();
 }
 
-// out = A.B^T (n x N, leading dimension ldo) from the BF16 hi/lo planes of A
-// (n x K) and B (N x K); same products and error as the probe's distances
-hipError_t launch_gemm_bf16x3(const unsigned short* Ah, const unsigned short* Al, int64_t n,
-                              const unsigned short* Bh, const unsigned short* Bl, int64_t N, int K,
+// Planes of the transpose of a K x N row-major matrix (rows j of N), 8
+// consecutive k per thread
+__global__ __launch_bounds__(256) void split_t_kernel(const float* __restrict__ x, int K, int N,
+                                                      unsigned short* __restrict__ planes)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= (int64_t)(K >> 3) * N) return;
+    const int j = (int)(i % N), k = (int)(i / N) * 8;
+    unsigned h[4], l[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        split2(x[(int64_t)(k + 2 * c) * N + j], x[(int64_t)(k + 2 * c + 1) * N + j], h[c], l[c]);
+    unsigned short* p = planes + plane_at(j, k, K);
+    *(uint4*)p = make_uint4(h[0], h[1], h[2], h[3]);
+    *(uint4*)(p + 512) = make_uint4(l[0], l[1], l[2], l[3]);
+}
+
+hipError_t launch_split_t(const float* x, int K, int N, unsigned short* planes, hipStream_t st)
+{
+    const int64_t n = (int64_t)(K >> 3) * N;
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(split_t_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, x, K, N, planes);
+    return hipGetLastError();
+}
+
+namespace {
+
+__device__ inline v8bf as_bf(const uint4& v) {
+    v8bf r;
+    __builtin_memcpy(&r, &v, 16);
+    return r;
+}
+
+// One output of a product of A's rows with the rows of B (N of them): EPI 1
+// squared distances ||a||^2 + ||b||^2 - 2 a.b, 2 negated inner products -a.b, 0 a.b
+struct MmOut {
+    const unsigned short* B;
+    int N;
+    int epi;
+    float* out;
+    int64_t ldo;
+    const float* bn2;
+};
+
+// The outputs of row tile rt and NT column tiles from ct: the rows' norms are
+// loaded together, and only the last row tile tests its rows.
+template <int NT>
+__device__ inline void store_tile(const v16f (&acc)[NT], const MmOut& o, const float* __restrict__ an2, int64_t n,
+                                  int64_t rt, int ct, int lane)
+{
+    float rn[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int64_t gr = 32 * rt + out_row(lane, r);
+        rn[r] = o.epi == 1 ? an2[gr < n ? gr : n - 1] : 0.0f;
+    }
+    const bool whole = 32 * rt + 32 <= n;
+#pragma unroll
+    for (int b = 0; b < NT; ++b) {
+        const int gc = 32 * (ct + b) + (lane & 31);
+        const float bn = o.epi == 1 && gc < o.N ? o.bn2[gc] : 0.0f;
+        if (gc >= o.N) continue;
+        float* p = o.out + (32 * rt + out_row(lane, 0)) * o.ldo + gc;
+        auto value = [&](int r) {
+            const float c = acc[b][r];
+            return o.epi == 1 ? (rn[r] + bn) - 2.0f * c : o.epi == 2 ? -c : c;
+        };
+        if (whole) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) p[(8 * (r >> 2) + (r & 3)) * o.ldo] = value(r);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (32 * rt + out_row(lane, r) < n) p[(8 * (r >> 2) + (r & 3)) * o.ldo] = value(r);
+        }
+    }
+}
+
+// Products of A (n x K planes) with the rows of two matrices in one launch:
+// the column blocks of o0, then those of o1 (the probe's distances and the
+// query rotation share A).  A wave owns MT x NT tiles of 32 x 32, a workgroup
+// 4 waves as WR x (4 / WR).  No LDS and no barrier: fragments go from L1/L2 to
+// registers, D chunks of K ahead, in a ring that is consumed and refilled in
+// place.  Workgroups are dealt to the 8 XCDs so that each takes a contiguous
+// range of column blocks (its slice of B stays in its L2) over all rows.
+template <int MT, int NT, int WR, int D>
+__global__ __launch_bounds__(256, 2) void mm_bf16x3_kernel(const unsigned short* __restrict__ A, int64_t n, int K,
+                                                           const float* __restrict__ an2, MmOut o0, MmOut o1,
+                                                           int cb0, int64_t rb, int64_t nblk)
+{
+    constexpr int WC = 4 / WR;
+    const int lane = threadIdx.x & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t per = (nblk + 7) >> 3, blk = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if ((int64_t)(blockIdx.x >> 3) >= per || blk >= nblk) return;
+    int cb = (int)(blk / rb);
+    const int64_t rt0 = ((blk - cb * rb) * WR + wid / WC) * MT;          // first row tile of the wave
+    const bool second = cb >= cb0;
+    const MmOut& o = second ? o1 : o0;
+    if (second) cb -= cb0;
+    const int ct0 = (cb * WC + wid % WC) * NT;                           // first column tile
+    const int64_t rtn = (n + 31) >> 5;
+    const int ctn = (o.N + 31) >> 5;
+    if (rt0 >= rtn || ct0 >= ctn) return;
+    const int S = K >> 4;                                                // chunks: a multiple of 4
+    const uint4* pa[MT];
+    const uint4* pb[NT];
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+        pa[a] = (const uint4*)A + (rt0 + a < rtn ? rt0 + a : rtn - 1) * S * 128 + lane;
+#pragma unroll
+    for (int b = 0; b < NT; ++b)
+        pb[b] = (const uint4*)o.B + (int64_t)(ct0 + b < ctn ? ct0 + b : ctn - 1) * S * 128 + lane;
+    v16f acc[MT][NT];
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int b = 0; b < NT; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
+    uint4 fa[D][MT][2], fb[D][NT][2];
+    auto load = [&](int d, int s) {
+#pragma unroll
+        for (int a = 0; a < MT; ++a) { fa[d][a][0] = pa[a][s * 128]; fa[d][a][1] = pa[a][s * 128 + 64]; }
+#pragma unroll
+        for (int b = 0; b < NT; ++b) { fb[d][b][0] = pb[b][s * 128]; fb[d][b][1] = pb[b][s * 128 + 64]; }
+    };
+#pragma unroll
+    for (int d = 0; d < D; ++d) load(d, D > 4 ? min(d, S - 1) : d);
+    for (int s0 = 0; s0 < S; s0 += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            if (D > 4 && s0 + d >= S) break;         // wave-uniform (S is a multiple of 4)
+            v8bf ah[MT], al[MT], bh[NT], bl[NT];
+#pragma unroll
+            for (int a = 0; a < MT; ++a) { ah[a] = as_bf(fa[d][a][0]); al[a] = as_bf(fa[d][a][1]); }
+#pragma unroll
+            for (int b = 0; b < NT; ++b) { bh[b] = as_bf(fb[d][b][0]); bl[b] = as_bf(fb[d][b][1]); }
+#pragma unroll
+            for (int a = 0; a < MT; ++a)
+#pragma unroll
+                for (int b = 0; b < NT; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[a], bh[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+            for (int a = 0; a < MT; ++a)
+#pragma unroll
+                for (int b = 0; b < NT; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bl[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+            for (int a = 0; a < MT; ++a)
+#pragma unroll
+                for (int b = 0; b < NT; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bh[b], acc[a][b], 0, 0, 0);
+            load(d, min(s0 + d + D, S - 1));         // past the end the last chunk again: no load is conditional
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);                // the epilogue's loads hold no registers through the loop
+#pragma unroll
+    for (int a = 0; a < MT; ++a) store_tile<NT>(acc[a], o, an2, n, rt0 + a, ct0, lane);
+}
+
+template <int MT, int NT, int WR, int D>
+hipError_t launch_mm_t(const unsigned short* A, int64_t n, int K, const float* an2, const MmOut& o0, const MmOut& o1,
+                       hipStream_t st)
+{
+    constexpr int BR = 32 * MT * WR, BC = 32 * NT * (4 / WR);
+    const int64_t rb = (n + BR - 1) / BR;
+    const int cb0 = (o0.N + BC - 1) / BC, cb1 = (o1.N + BC - 1) / BC;
+    const int64_t nblk = rb * (cb0 + cb1);
+    hipLaunchKernelGGL((mm_bf16x3_kernel<MT, NT, WR, D>), dim3((unsigned)((nblk + 7) / 8 * 8)), dim3(256), 0, st, A, n,
+                       K, an2, o0, o1, cb0, rb, nblk);
+    return hipGetLastError();
+}
+
+// The same products for many rows: 4 waves take 256 x 128 outputs, 4 x 2 tiles
+// each, with both operands in LDS (two buffers of one K chunk, 24 KB each, so
+// two workgroups share a CU and fill each other's waits).  The fragments are
+// copied global -> LDS without registers; a wave has read a stage's fragments
+// before it issues the next stage's copies, so the compiler's wait for copies in
+// front of LDS reads never meets one in flight.  One barrier per chunk.
+constexpr int kBigR = 8, kBigC = 4;                   // row and column tiles of 32 per workgroup
+constexpr int kBigStage = (kBigR + kBigC) * 2048;     // bytes of a stage: hi and lo fragment per tile
+
+typedef const __attribute__((address_space(1))) void* gptr;
+typedef __attribute__((address_space(3))) void* lptr;
+
+// the 2 KB of a (tile, chunk) from global memory to LDS by one wave
+__device__ inline void copy_chunk(const uint4* g, char* l) {
+    __builtin_amdgcn_global_load_lds((gptr)g, (lptr)l, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((gptr)(g + 64), (lptr)(l + 1024), 16, 0, 0);
+}
+
+__global__ __launch_bounds__(256, 2) void mm_big_kernel(const unsigned short* __restrict__ A, int64_t n, int K,
+                                                        const float* __restrict__ an2, MmOut o0, MmOut o1, int cb0,
+                                                        int64_t rb, int64_t nblk)
+{
+    __shared__ __align__(16) char smem[2][kBigStage];
+    const int lane = threadIdx.x & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t per = (nblk + 7) >> 3, blk = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if ((int64_t)(blockIdx.x >> 3) >= per || blk >= nblk) return;
+    int cb = (int)(blk / rb);
+    const int64_t rt0 = (blk - cb * rb) * kBigR;
+    const bool second = cb >= cb0;
+    const MmOut& o = second ? o1 : o0;
+    if (second) cb -= cb0;
+    const int ct0 = cb * kBigC;
+    const int64_t rtn = (n + 31) >> 5;
+    const int ctn = (o.N + 31) >> 5;
+    const int S = K >> 4;
+    // wave w copies row tiles 2w and 2w + 1 and column tile w
+    const uint4* ga[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+        ga[u] = (const uint4*)A + (rt0 + 2 * wid + u < rtn ? rt0 + 2 * wid + u : rtn - 1) * S * 128 + lane;
+    const uint4* gb = (const uint4*)o.B + (int64_t)(ct0 + wid < ctn ? ct0 + wid : ctn - 1) * S * 128 + lane;
+    auto copy = [&](int s) {
+        char* l = smem[s & 1];
+        copy_chunk(ga[0] + s * 128, l + (2 * wid) * 2048);
+        copy_chunk(ga[1] + s * 128, l + (2 * wid + 1) * 2048);
+        copy_chunk(gb + s * 128, l + (kBigR + wid) * 2048);
+    };
+    const int wr = (wid >> 1) * 4, wc = (wid & 1) * 2;
+    v16f acc[4][2];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
+    copy(0);
+    for (int s = 0; s < S; ++s) {
+        const char* cur = smem[s & 1] + lane * 16;
+        __syncthreads();                              // this chunk is in LDS; the other buffer's readers are done
+        auto frag = [&](int tile, int plane) {
+            v8bf v;
+            __builtin_memcpy(&v, cur + tile * 2048 + plane * 1024, 16);
+            return v;
+        };
+        v8bf ah[4], al[4], bh[2], bl[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) { bh[b] = frag(kBigR + wc + b, 0); bl[b] = frag(kBigR + wc + b, 1); }
+#pragma unroll
+        for (int a = 0; a < 4; ++a) { ah[a] = frag(wr + a, 0); al[a] = frag(wr + a, 1); }
+        __builtin_amdgcn_sched_barrier(0);
+        if (s + 1 < S) copy(s + 1);
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[a], bh[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bl[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bh[b], acc[a][b], 0, 0, 0);
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) store_tile<2>(acc[a], o, an2, n, rt0 + wr + a, ct0 + wc, lane);
+}
+
+hipError_t launch_mm_big(const unsigned short* A, int64_t n, int K, const float* an2, const MmOut& o0, const MmOut& o1,
+                         hipStream_t st)
+{
+    const int64_t rb = (n + 32 * kBigR - 1) / (32 * kBigR);
+    const int cb0 = (o0.N + 32 * kBigC - 1) / (32 * kBigC), cb1 = (o1.N + 32 * kBigC - 1) / (32 * kBigC);
+    const int64_t nblk = rb * (cb0 + cb1);
+    hipLaunchKernelGGL(mm_big_kernel, dim3((unsigned)((nblk + 7) / 8 * 8)), dim3(256), 0, st, A, n, K, an2, o0, o1, cb0,
+                       rb, nblk);
+    return hipGetLastError();
+}
+
+// The 256 x 128 tiles where they give every CU one (10,000 x 4,864 x 768: 199
+// us against 257 with 2 x 2 tiles per wave and no LDS, 270 with 128 x 128 tiles
+// staged through registers; 2,000 rows: 56 against 61).  Else every wave loads
+// its own fragments: 2 x 2 tiles where that leaves two waves for every SIMD,
+// 2 x 1 down to one (1000 x 5056 x 960: 46 us against 62), below that 1 x 1
+// with the loads 8 chunks ahead, as the chain of one wave is what counts (1 x
+// 1,792 x 768: 10 us against 51 with 128 x 128 tiles; 500 x 4,096 x 3072: 60
+// against 240).
+hipError_t launch_mm(const unsigned short* A, int64_t n, int K, const float* an2, const MmOut& o0, const MmOut& o1,
+                     hipStream_t st)
+{
+    const int64_t waves = (n + 63) / 64 * ((o0.N + 63) / 64 + (o1.N + 63) / 64);
+    if ((n + 255) / 256 * ((o0.N + 127) / 128 + (o1.N + 127) / 128) >= 256)
+        return launch_mm_big(A, n, K, an2, o0, o1, st);
+    if (waves >= 2048) return launch_mm_t<2, 2, 2, 2>(A, n, K, an2, o0, o1, st);
+    if (n <= 32) return launch_mm_t<1, 1, 1, 8>(A, n, K, an2, o0, o1, st);
+    if (waves >= 1024) return launch_mm_t<2, 1, 2, 2>(A, n, K, an2, o0, o1, st);
+    return launch_mm_t<1, 1, 2, 8>(A, n, K, an2, o0, o1, st);
+}
+
+}  // namespace
+
+// out = A.B^T (n x N, leading dimension ldo) from the planes of A (n x K) and B (N x K)
+hipError_t launch_gemm_bf16x3(const unsigned short* A, int64_t n, const unsigned short* B, int64_t N, int K,
                               float* out, int64_t ldo, hipStream_t st)
 {
     if (n <= 0 || N <= 0) return hipSuccess;
-    dim3 grid((unsigned)((N + BN - 1) / BN), (unsigned)((n + BM - 1) / BM));
-    hipLaunchKernelGGL(sqdist_bf16x3_kernel<0>, grid, dim3(256), 0, st, Ah, Al, n, K, Bh, Bl, (int)N, out, ldo,
-                       (const float*)nullptr, (const float*)nullptr);
-    return hipGetLastError();
+    return launch_mm(A, n, K, nullptr, MmOut{B, (int)N, 0, out, ldo, nullptr}, MmOut{B, 0, 0, nullptr, 0, nullptr}, st);
 }
 
-// Rows of X (n x K, K a multiple of 4) -> their BF16 hi/lo planes (as
-// split_bf16_kernel; not with PLANES = false) and squared norms ||x||^2 (FP32);
-// one wave per row, 4 consecutive elements per lane
-template <bool PLANES>
-__global__ __launch_bounds__(256) void split_norm_kernel(const float* __restrict__ X, int64_t n, int K,
-                                                         unsigned short* __restrict__ hi,
-                                                         unsigned short* __restrict__ lo, float* __restrict__ n2)
+// The probe's distances D (n x N; negated inner products with neg_ip) and,
+// when R is given, the rotation rot = A.R^T (n x NR, leading dimension NR).
+hipError_t launch_probe_products(const unsigned short* A, int64_t n, int K, const float* an2, const unsigned short* B,
+                                 int64_t N, const float* bn2, int neg_ip, float* D, const unsigned short* R, int NR,
+                                 float* rot, hipStream_t st)
 {
-    const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (r >= n) return;
-    float s = 0.0f;
-    for (int k = 4 * lane; k < K; k += 256) {
-        const int64_t i = r * (int64_t)K + k;
-        const float4 v = *(const float4*)(X + i);
-        const float xv[4] = {v.x, v.y, v.z, v.w};
-        unsigned h[4], l[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            s += xv[c] * xv[c];
-            if constexpr (PLANES) {
-                h[c] = f2bf(xv[c]);
-                l[c] = f2bf(xv[c] - __uint_as_float(h[c] << 16));
-            }
-        }
-        if constexpr (PLANES) {
-            *(uint2*)(hi + i) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-            *(uint2*)(lo + i) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
-        }
-    }
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    if (lane == 0) n2[r] = s;
-}
-
-hipError_t launch_split_norm(const float* X, int64_t n, int K, unsigned short* hi, unsigned short* lo, float* n2,
-                             hipStream_t st)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(split_norm_kernel<true>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, X, n, K, hi, lo, n2);
-    return hipGetLastError();
-}
-
-// the squared norms alone (the same sums)
-hipError_t launch_norm(const float* X, int64_t n, int K, float* n2, hipStream_t st)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(split_norm_kernel<false>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, X, n, K,
-                       (unsigned short*)nullptr, (unsigned short*)nullptr, n2);
-    return hipGetLastError();
-}
-
-hipError_t launch_split_bf16(const float* x, int64_t n, unsigned short* hi, unsigned short* lo, hipStream_t st)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(split_bf16_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, st, x, n, hi, lo);
-    return hipGetLastError();
+    if (n <= 0 || N <= 0) return hipSuccess;
+    return launch_mm(A, n, K, an2, MmOut{B, (int)N, neg_ip ? 2 : 1, D, N, bn2},
+                     MmOut{R ? R : B, R ? NR : 0, 0, rot, NR, nullptr}, st);
 }
 
 // Nearest column of every row (the assignment of rows to centroids): the
-// smallest of the distances that sqdist_bf16x3_kernel<EPI> would write, ties to
-// the lower column, without writing them.  A is read as FP32 and split into its
-// BF16 planes on the way to LDS (the same values as split_bf16_kernel's).
+// smallest of the distances that mm_bf16x3_kernel would write with this EPI (1
+// or 2), ties to the lower column, without writing them.
 //
-// A workgroup takes 128 rows and a range of column tiles; every lane keeps the
-// best of its columns for its 32 rows in registers over the whole range, so the
-// cross-lane work is done once per workgroup.  best (n slots, all ones) holds
-// (key of the distance, column) when the columns are split over gridDim.y > 1
-// workgroups; with one, the columns go straight to out.
-// Bound: LDS traffic and matrix cores, as the probe's GEMM (200,000 x 1024 x
-// 768: 1.18 ms for the product, and the 0.8 GB of distances that the separate
-// selection wrote, allocated and read back (0.84 ms) are gone).
+// A workgroup takes 128 rows and a range of column tiles (128 wide).  A is read
+// as FP32 and split into its planes on the way to LDS (two buffers, one barrier
+// per 32 of K); B's fragments go straight to registers.  The product is taken
+// transposed (MFMA rows: columns of B, lanes: rows of A), so a row's candidates
+// lie in one lane's registers and the running minimum costs no cross-lane work;
+// the two half-waves and the two waves of a row meet in LDS once per workgroup.
+// 200,000 x 1024 x 768: 1.13 ms, 840 TFLOP/s (1.53 with B staged in LDS too and
+// the rounding in integer arithmetic; 256 x 128 tiles spill and take 1.2-1.7).
+// best (n slots, all ones) holds (key of the distance, column) when the columns
+// are split over gridDim.y > 1 workgroups; with one, they go straight to out.
 template <int EPI>
 __global__ __launch_bounds__(256, 2) void assign_bf16x3_kernel(
-    const float* __restrict__ A, int64_t n, int K, const unsigned short* __restrict__ Bhg,
-    const unsigned short* __restrict__ Blg, int N, const float* __restrict__ an2, const float* __restrict__ bn2,
-    int tiles_per_block, unsigned long long* __restrict__ best, int32_t* __restrict__ out)
+    const float* __restrict__ A, int64_t n, int K, const unsigned short* __restrict__ B, int N,
+    const float* __restrict__ an2, const float* __restrict__ bn2, int tiles_per_block,
+    unsigned long long* __restrict__ best, int32_t* __restrict__ out)
 {
-    constexpr int BK = 32, LD = BK + 8;
-    __shared__ __align__(16) unsigned short Ah[BM][LD], Al[BM][LD], Bh[BN][LD], Bl[BN][LD];
-    __shared__ float s_an[BM];
+    constexpr int BK = 32;
+    __shared__ __align__(16) unsigned short As[2][4][2][1024];           // buffer, row tile, chunk, hi | lo fragment
+    __shared__ float s_bn[BN];
     __shared__ unsigned long long s_best[BM];
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t row0 = (int64_t)blockIdx.x * BM;
-    const int wm = (wid >> 1) * 64, wn = (wid & 1) * 64;
-    if (tid < BM) {
-        s_an[tid] = row0 + tid < n && EPI == 1 ? an2[row0 + tid] : 0.0f;
-        s_best[tid] = ~0ull;
-    }
-    // per K-tile: thread tid moves k = 8 (tid % 4) .. + 8 of rows tid/4 and tid/4 + 64
-    const int m0 = tid >> 2, m1 = m0 + 64, kq = (tid & 3) * 8;
-    const bool a0 = row0 + m0 < n, a1 = row0 + m1 < n;
-    const float* pa0 = A + (row0 + m0) * K + kq;
-    const float* pa1 = A + (row0 + m1) * K + kq;
+    const int wm = (wid >> 1) * 2, wn = (wid & 1) * 2;                   // first row / column tile of the wave
+    if (tid < BM) s_best[tid] = ~0ull;
+    // thread tid moves 4 k of row tid / 8 of every row tile: 8 lanes a row's 128
+    // bytes of a stage
+    const int m = tid >> 3, kq = 4 * (tid & 7);
+    const float* pa = A + (row0 + m) * K + kq;
+    unsigned short* const la = &As[0][0][kq >> 4][(m + 32 * ((kq >> 3) & 1)) * 8 + (kq & 7)];
+    const int S = K >> 4, ctn = (N + 31) >> 5;
     const int tile0 = blockIdx.y * tiles_per_block, tile1 = min(tile0 + tiles_per_block, (N + BN - 1) / BN);
-    float bv[2][16];
-    int bc[2][16];                                   // column tile (32 wide) of the best
+    float rn[2];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < 2; ++a) {
+        const int64_t gr = row0 + 32 * (wm + a) + (lane & 31);
+        rn[a] = EPI == 1 && gr < n ? an2[gr] : 0.0f;
+    }
+    // nothing below +inf (NaN is not): the lane's first column
+    float bv[2] = {__builtin_huge_valf(), __builtin_huge_valf()};
+    const int first = tile0 * BN + 32 * wn + out_row(lane, 0);
+    int bc[2] = {first, first};
+    float4 f[4];
+    auto load_a = [&](int k) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { bv[a][r] = __builtin_huge_valf(); bc[a][r] = (tile0 * BN + wn) >> 5; }
-    auto ldf = [](const float* p, bool ok, float4& v0, float4& v1) {
-        v0 = v1 = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (ok) { v0 = *(const float4*)p; v1 = *(const float4*)(p + 4); }
+        for (int u = 0; u < 4; ++u)
+            f[u] = row0 + m + 32 * u < n ? *(const float4*)(pa + (int64_t)32 * u * K + k) : make_float4(0.f, 0.f, 0.f, 0.f);
     };
-    auto put = [](unsigned short* ph, unsigned short* pl, const float4& v0, const float4& v1) {
-        const float x[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-        unsigned h[8], l[8];
+    auto store_a = [&](int buf) {
+        unsigned short* p = la + buf * (4 * 2 * 1024);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            h[c] = f2bf(x[c]);
-            l[c] = f2bf(x[c] - __uint_as_float(h[c] << 16));
+        for (int u = 0; u < 4; ++u) {
+            uint2 h, l;
+            split2(f[u].x, f[u].y, h.x, l.x);
+            split2(f[u].z, f[u].w, h.y, l.y);
+            *(uint2*)(p + u * 2048) = h;
+            *(uint2*)(p + u * 2048 + 512) = l;
         }
-        *(uint4*)ph = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
-        *(uint4*)pl = make_uint4(l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16));
     };
     for (int tile = tile0; tile < tile1; ++tile) {
-        const int col0 = tile * BN;
-        const bool b0 = col0 + m0 < N, b1 = col0 + m1 < N;
-        const unsigned short* pb0h = Bhg + (int64_t)(col0 + m0) * K + kq;
-        const unsigned short* pb1h = Bhg + (int64_t)(col0 + m1) * K + kq;
-        const unsigned short* pb0l = Blg + (int64_t)(col0 + m0) * K + kq;
-        const unsigned short* pb1l = Blg + (int64_t)(col0 + m1) * K + kq;
+        const uint4* pb[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) pb[b] = (const uint4*)B + (int64_t)min(4 * tile + wn + b, ctn - 1) * S * 128 + lane;
+        uint4 fb[2][2][2];
+        auto load_b = [&](int s, uint4 (&d)[2][2]) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b) { d[b][0] = pb[b][s * 128]; d[b][1] = pb[b][s * 128 + 64]; }
+        };
         v16f acc[2][2];
 #pragma unroll
         for (int a = 0; a < 2; ++a)
@@ -483,87 +708,73 @@ __global__ __launch_bounds__(256, 2) void assign_bf16x3_kernel(
             for (int b = 0; b < 2; ++b)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
-        float4 f0, f1, f2, f3;
-        uint4 r4, r5, r6, r7;
-        auto load = [&](int k) {
-            ldf(pa0 + k, a0, f0, f1);
-            ldf(pa1 + k, a1, f2, f3);
-            r4 = ld16(pb0h + k, b0); r5 = ld16(pb1h + k, b1); r6 = ld16(pb0l + k, b0); r7 = ld16(pb1l + k, b1);
-        };
-        auto store = [&]() {
-            put(&Ah[m0][kq], &Al[m0][kq], f0, f1);
-            put(&Ah[m1][kq], &Al[m1][kq], f2, f3);
-            *(uint4*)&Bh[m0][kq] = r4; *(uint4*)&Bh[m1][kq] = r5; *(uint4*)&Bl[m0][kq] = r6; *(uint4*)&Bl[m1][kq] = r7;
-        };
-        load(0);
-        store();
+        load_b(0, fb[0]);
+        load_b(1, fb[1]);
+        load_a(0);
+        __syncthreads();                             // the last tile's reads of LDS are done
+        store_a(0);
+        if (tid < BN) s_bn[tid] = EPI == 1 && tile * BN + tid < N ? bn2[tile * BN + tid] : 0.0f;
         __syncthreads();
+        int cur = 0;
         for (int k0 = 0; k0 < K; k0 += BK) {
             const bool more = k0 + BK < K;
-            if (more) load(k0 + BK);                // into registers while this K-tile is multiplied
+            if (more) load_a(k0 + BK);
 #pragma unroll
-            for (int ks = 0; ks < BK; ks += 16) {
-                const int kk = ks + 8 * (lane >> 5);
+            for (int c = 0; c < 2; ++c) {
                 v8bf ah[2], al[2], bh[2], bl[2];
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    __builtin_memcpy(&ah[t], &Ah[wm + 32 * t + (lane & 31)][kk], 16);
-                    __builtin_memcpy(&al[t], &Al[wm + 32 * t + (lane & 31)][kk], 16);
-                    __builtin_memcpy(&bh[t], &Bh[wn + 32 * t + (lane & 31)][kk], 16);
-                    __builtin_memcpy(&bl[t], &Bl[wn + 32 * t + (lane & 31)][kk], 16);
+                for (int a = 0; a < 2; ++a) {
+                    __builtin_memcpy(&ah[a], &As[cur][wm + a][c][lane * 8], 16);
+                    __builtin_memcpy(&al[a], &As[cur][wm + a][c][512 + lane * 8], 16);
                 }
 #pragma unroll
-                for (int a = 0; a < 2; ++a)
-#pragma unroll
-                    for (int b = 0; b < 2; ++b) {
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[a], bh[b], acc[a][b], 0, 0, 0);
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bl[b], acc[a][b], 0, 0, 0);
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bh[b], acc[a][b], 0, 0, 0);
-                    }
-            }
-            __syncthreads();                        // every read of this K-tile is done
-            if (more) {
-                store();
-                __syncthreads();
-            }
-        }
-        // columns ascend over tiles and b, so a strict comparison keeps the lowest
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int gc = col0 + wn + 32 * b + (lane & 31);
-            if (gc < N) {
-                const float bn = EPI == 1 ? bn2[gc] : 0.0f;
+                for (int b = 0; b < 2; ++b) { bh[b] = as_bf(fb[c][b][0]); bl[b] = as_bf(fb[c][b][1]); }
 #pragma unroll
                 for (int a = 0; a < 2; ++a)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const float v = EPI == 1 ? (s_an[wm + 32 * a + out_row(lane, r)] + bn) - 2.0f * acc[a][b][r]
-                                                 : -acc[a][b][r];
-                        const bool better = v < bv[a][r];
-                        bv[a][r] = better ? v : bv[a][r];
-                        bc[a][r] = better ? (col0 + wn + 32 * b) >> 5 : bc[a][r];
-                    }
+                    for (int b = 0; b < 2; ++b)
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh[b], al[a], acc[a][b], 0, 0, 0);
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bl[b], ah[a], acc[a][b], 0, 0, 0);
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh[b], ah[a], acc[a][b], 0, 0, 0);
+                load_b(min((k0 >> 4) + 2 + c, S - 1), fb[c]);
             }
+            if (more) store_a(cur ^ 1);
+            __syncthreads();
+            cur ^= 1;
         }
+        // columns ascend over tiles, b and r, so a strict comparison keeps the lowest
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int lc = 32 * (wn + b) + out_row(lane, r), gc = tile * BN + lc;
+                const float bn = s_bn[lc];
+                if (gc < N) {
+#pragma unroll
+                    for (int a = 0; a < 2; ++a) {
+                        const float v = EPI == 1 ? (rn[a] + bn) - 2.0f * acc[a][b][r] : -acc[a][b][r];
+                        const bool better = v < bv[a];
+                        bv[a] = better ? v : bv[a];
+                        bc[a] = better ? gc : bc[a];
+                    }
+                }
+            }
     }
-    // over the 32 lanes of a row, then the two waves of a row
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const unsigned u = __float_as_uint(bv[a][r]);
-            unsigned key = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-            unsigned col = (unsigned)(bc[a][r] * 32 + (lane & 31));
-            if (col >= (unsigned)N) key = 0xFFFFFFFFu;              // a lane without columns
-            for (int o = 16; o > 0; o >>= 1) {
-                const unsigned ok = __shfl_xor(key, o), oc = __shfl_xor(col, o);
-                const bool take = ok < key || (ok == key && oc < col);
-                key = take ? ok : key;
-                col = take ? oc : col;
-            }
-            if ((lane & 31) == 0)
-                atomicMin(&s_best[wm + 32 * a + out_row(lane, r)], ((unsigned long long)key << 32) | col);
-        }
+    for (int a = 0; a < 2; ++a) {
+        const unsigned u = __float_as_uint(bv[a]);
+        const unsigned key = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+        if (bc[a] < N)
+            atomicMin(&s_best[32 * (wm + a) + (lane & 31)], ((unsigned long long)key << 32) | (unsigned)bc[a]);
+    }
     __syncthreads();
     if (tid < BM && row0 + tid < n) {
         if (gridDim.y == 1) out[row0 + tid] = (int32_t)(unsigned)s_best[tid];
@@ -580,52 +791,33 @@ __global__ void best_column_kernel(const unsigned long long* best, int64_t n, in
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) out[i] = (int32_t)(unsigned)best[i];
 }
-// Workgroups that share a row tile: enough for about three rounds of the
-// resident ones (two per CU) where the rows alone do not give them.
-int assign_split(int64_t n, int64_t N) {
+// Column tiles per workgroup: few enough that there are some 4,000 workgroups
+// (three are resident per CU; 200,000 x 1024 x 768: 1.13 ms, 300,000 x 7000 x
+// 128: 2.0 against 2.2 with 2,000).
+int assign_tiles(int64_t n, int64_t N) {
     const int64_t rows = (n + BM - 1) / BM, tiles = (N + BN - 1) / BN;
-    return (int)std::min<int64_t>(tiles, std::max<int64_t>(1, 1536 / rows));
+    return (int)std::min(tiles, std::max<int64_t>(1, rows * tiles / 4096));
 }
 }  // namespace
 
 // scratch of launch_assign: the rows' (distance, column) slots when columns are split
 size_t assign_scratch_bytes(int64_t n, int64_t N)
 {
-    return assign_split(n, N) > 1 ? sizeof(unsigned long long) * (size_t)n : 0;
+    return assign_tiles(n, N) < (N + BN - 1) / BN ? sizeof(unsigned long long) * (size_t)n : 0;
 }
 
-hipError_t launch_assign(const float* A, int64_t n, int K, const unsigned short* Bh, const unsigned short* Bl,
-                         int64_t N, const float* an2, const float* bn2, int neg_ip, int32_t* out, void* scratch,
-                         hipStream_t st)
+hipError_t launch_assign(const float* A, int64_t n, int K, const unsigned short* B, int64_t N, const float* an2,
+                         const float* bn2, int neg_ip, int32_t* out, void* scratch, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
     unsigned long long* best = (unsigned long long*)scratch;
-    const int tiles = (int)((N + BN - 1) / BN), split = assign_split(n, N), per = (tiles + split - 1) / split;
-    const dim3 grid((unsigned)((n + BM - 1) / BM), (unsigned)((tiles + per - 1) / per));
+    const int per = assign_tiles(n, N);
+    const dim3 grid((unsigned)((n + BM - 1) / BM), (unsigned)(((N + BN - 1) / BN + per - 1) / per));
     const dim3 g1((unsigned)((n + 255) / 256));
     if (grid.y > 1) hipLaunchKernelGGL(fill_u64_kernel, g1, dim3(256), 0, st, best, n);
-    if (neg_ip)
-        hipLaunchKernelGGL(assign_bf16x3_kernel<2>, grid, dim3(256), 0, st, A, n, K, Bh, Bl, (int)N, an2, bn2, per,
-                           best, out);
-    else
-        hipLaunchKernelGGL(assign_bf16x3_kernel<1>, grid, dim3(256), 0, st, A, n, K, Bh, Bl, (int)N, an2, bn2, per,
-                           best, out);
+    auto* k = neg_ip ? assign_bf16x3_kernel<2> : assign_bf16x3_kernel<1>;
+    hipLaunchKernelGGL(k, grid, dim3(256), 0, st, A, n, K, B, (int)N, an2, bn2, per, best, out);
     if (grid.y > 1) hipLaunchKernelGGL(best_column_kernel, g1, dim3(256), 0, st, best, n, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_sqdist_pre(const unsigned short* Ah, const unsigned short* Al, int64_t n,
-                             const unsigned short* Bh, const unsigned short* Bl, int64_t N, int K,
-                             const float* an2, const float* bn2, float* out, hipStream_t st, int neg_ip)
-{
-    if (n <= 0 || N <= 0) return hipSuccess;
-    dim3 grid((unsigned)((N + BN - 1) / BN), (unsigned)((n + BM - 1) / BM));
-    if (neg_ip)
-        hipLaunchKernelGGL(sqdist_bf16x3_kernel<2>, grid, dim3(256), 0, st, Ah, Al, n, K, Bh, Bl, (int)N, out,
-                           (int64_t)N, an2, bn2);
-    else
-        hipLaunchKernelGGL(sqdist_bf16x3_kernel<1>, grid, dim3(256), 0, st, Ah, Al, n, K, Bh, Bl, (int)N, out,
-                           (int64_t)N, an2, bn2);
     return hipGetLastError();
 }
 

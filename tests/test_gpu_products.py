@@ -1,0 +1,58 @@
+"""The BF16 hi/lo products of the probe and the rotation at the edges of every
+tile shape they choose (one row, one tile, few rows, 2 x 1 and 2 x 2 tiles per
+wave, 256 x 128 tiles through LDS), against FP64.
+
+Bound per value: each product is off by at most 2^-15 |a_i b_i| (split residuals
+and the dropped lo.lo) and the FP32 sum of 3 K terms by its forward error bound;
+a distance takes twice that and the rounding of its three terms.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2409_09913_amd import erq
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+DEV = torch.device("cuda:0")
+U = 2.0 ** -24
+
+
+@pytest.mark.parametrize("n,nl,dp", [(1, 1, 64), (1, 33, 64), (31, 300, 128), (32, 129, 192), (33, 65, 64),
+                                     (129, 700, 320), (700, 5000, 64), (1025, 4100, 128), (5000, 300, 64),
+                                     (2049, 8200, 64), (4100, 2055, 128)])
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+def test_probe_distances(n, nl, dp, metric):
+    print("probe products", n, nl, dp, metric, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(n + nl)
+    q = torch.randn((n, dp), device=DEV, generator=g)
+    c = torch.randn((nl, dp), device=DEV, generator=g)
+    k = min(nl, 1024)
+    probes, d = erq.coarse_probe(q, c, k, with_dist=True, metric=metric)
+    p = probes.long()
+    ip = (q.double() @ c.double().T).gather(1, p)
+    mag = (q.double().abs() @ c.double().abs().T).gather(1, p)
+    err = (2.0 ** -15 + 3 * dp * U / (1 - 3 * dp * U)) * mag
+    if metric == "l2":
+        n2 = (q.double() ** 2).sum(1)[:, None] + (c.double() ** 2).sum(1)[p]
+        want, tol = n2 - 2 * ip, 2 * err + (dp + 3) * U * (n2 + 2 * mag)
+    else:
+        want, tol = -ip, err
+    assert bool(((d.double() - want).abs() <= tol).all())
+    assert bool((d[:, 1:] >= d[:, :-1]).all())
+    if k == nl:                                       # every column once
+        assert torch.equal(p.sort(1).values, torch.arange(nl, device=DEV).expand(n, nl))
+
+
+@pytest.mark.parametrize("n,dp", [(1, 64), (33, 128), (257, 192), (3000, 128), (9000, 960)])
+def test_rotation(n, dp):
+    g = torch.Generator(device=DEV).manual_seed(n)
+    x = torch.randn((n, dp), device=DEV, generator=g)
+    P = torch.linalg.qr(torch.randn((dp, dp), device=DEV, generator=g))[0].contiguous()
+    got = erq.rotate(x, P, precision=2).double()
+    want = x.double() @ P.double()
+    mag = x.double().abs() @ P.double().abs()
+    assert bool(((got - want).abs() <= (2.0 ** -15 + 3 * dp * U / (1 - 3 * dp * U)) * mag).all())
