@@ -180,6 +180,84 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(
         }
 }
 
+// out = A.B (B K x N row-major) for few rows, on v_mfma_f32_16x16x4_f32: a wave
+// takes MT x NT tiles of 16 x 16 and loads its own operands, D steps of 4 k
+// ahead, without LDS.  An FP32 matrix-core output is one chain of fused
+// multiply-adds over k ascending whatever the tile shape, so a row gets the same
+// bits here as from gemm_f32_kernel (tests compare them); the 16 x 16 x 4 form
+// takes 32 cycles for 4 k where 32 x 32 x 2 takes 64 for 2, and a lone wave's
+// time is that chain.
+template <int MT, int NT, int D>
+__global__ __launch_bounds__(64) void gemm_f32_small_kernel(const float* __restrict__ A, int64_t n, int K,
+                                                            const float* __restrict__ B, int N,
+                                                            float* __restrict__ out, int64_t ldo)
+{
+    const int lane = threadIdx.x, c = lane & 15, h = lane >> 4;
+    const int64_t row0 = (int64_t)blockIdx.y * (16 * MT);
+    const int col0 = blockIdx.x * (16 * NT);
+    const float* pa[MT];
+    const float* pb[NT];
+#pragma unroll
+    for (int a = 0; a < MT; ++a) {
+        const int64_t r = row0 + 16 * a + c;
+        pa[a] = A + (r < n ? r : n - 1) * K + h;
+    }
+#pragma unroll
+    for (int b = 0; b < NT; ++b) {
+        const int j = col0 + 16 * b + c;
+        pb[b] = B + (int64_t)h * N + (j < N ? j : N - 1);
+    }
+    v4f acc[MT][NT];
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int b = 0; b < NT; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[a][b][r] = 0.0f;
+    float fa[D][MT], fb[D][NT];
+    auto load = [&](int d, int s) {
+#pragma unroll
+        for (int a = 0; a < MT; ++a) fa[d][a] = pa[a][4 * s];
+#pragma unroll
+        for (int b = 0; b < NT; ++b) fb[d][b] = pb[b][(int64_t)4 * s * N];
+    };
+    const int S = K >> 2;                             // a multiple of 16, and D of 16's divisors
+#pragma unroll
+    for (int d = 0; d < D; ++d) load(d, d);
+    for (int s0 = 0; s0 < S; s0 += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+#pragma unroll
+            for (int a = 0; a < MT; ++a)
+#pragma unroll
+                for (int b = 0; b < NT; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[d][a], fb[d][b], acc[a][b], 0, 0, 0);
+            load(d, s0 + D < S ? s0 + D + d : s0 + d);   // past the end the last steps again
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) {
+            const int j = col0 + 16 * b + c;
+            if (j >= N) continue;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int64_t i = row0 + 16 * a + 4 * h + r;
+                if (i < n) out[i * ldo + j] = acc[a][b][r];
+            }
+        }
+}
+
+template <int MT, int NT, int D>
+hipError_t launch_gemm_small(const float* A, int64_t n, int K, const float* B, int N, float* out, int64_t ldo,
+                             hipStream_t st)
+{
+    const dim3 grid((unsigned)((N + 16 * NT - 1) / (16 * NT)), (unsigned)((n + 16 * MT - 1) / (16 * MT)));
+    hipLaunchKernelGGL((gemm_f32_small_kernel<MT, NT, D>), grid, dim3(64), 0, st, A, n, K, B, N, out, ldo);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_gemm(const float* A, int64_t n, int K, const float* B, int N, int b_trans,
@@ -187,6 +265,13 @@ hipError_t launch_gemm(const float* A, int64_t n, int K, const float* B, int N, 
 {
     if (n <= 0 || N <= 0) return hipSuccess;
     dim3 grid((unsigned)((N + BN - 1) / BN), (unsigned)((n + BM - 1) / BM));
+    // Few 128 x 128 tiles leave CUs idle behind K / 16 staged steps.  768 x 768,
+    // us against the tiles' 71: 1 row 8.5, 128 rows 14, 512 rows 36, 1000 rows 43,
+    // 2,000 rows (96 tiles) 75.  1 x 1 tiles of 16 up to two waves per SIMD.
+    if (precision != 1 && !b_trans && (int64_t)grid.x * grid.y < 96) {
+        if ((n + 15) / 16 * ((N + 15) / 16) < 2048) return launch_gemm_small<1, 1, 16>(A, n, K, B, N, out, ldo, st);
+        return launch_gemm_small<2, 2, 8>(A, n, K, B, N, out, ldo, st);
+    }
     if (precision == 1)
         hipLaunchKernelGGL(gemm_bf16_kernel, grid, dim3(256), 0, st, A, n, K, B, N, b_trans, out, ldo);
     else

@@ -56,3 +56,15 @@ def test_rotation(n, dp):
     want = x.double() @ P.double()
     mag = x.double().abs() @ P.double().abs()
     assert bool(((got - want).abs() <= (2.0 ** -15 + 3 * dp * U / (1 - 3 * dp * U)) * mag).all())
+
+
+@pytest.mark.parametrize("dp", [64, 128, 320, 768, 1088])
+def test_fp32_rotation_does_not_depend_on_the_batch(dp):
+    """One chain of fused multiply-adds per output, whatever tile shape the batch gets."""
+    g = torch.Generator(device=DEV).manual_seed(dp)
+    x = torch.randn((14_000, dp), device=DEV, generator=g) * torch.exp(2 * torch.randn((14_000, 1), device=DEV, generator=g))
+    P = torch.randn((dp, dp), device=DEV, generator=g)
+    want = erq.rotate(x, P).view(torch.int32)
+    for n in (1, 15, 17, 33, 500, 1400, 3001):
+        got = erq.rotate(x[:n].contiguous(), P).view(torch.int32)
+        assert torch.equal(got, want[:n]), n
