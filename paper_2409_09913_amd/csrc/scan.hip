@@ -222,6 +222,13 @@ __device__ inline void load_query_scalars(float* s_s2, float* s_hd, int* s_ss, i
 
 constexpr int kRowLoads = 12;
 
+// a 64-bit value that is the same in all lanes, in scalar registers
+__device__ inline int64_t uniform64(int64_t v) {
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)((uint64_t)v >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
 // With LO (NQT = 2), rows [kQT, 2 kQT) hold the low planes of the queries of
 // rows [0, kQT).
 template <int NQT, bool LO = false>
@@ -258,6 +265,35 @@ __device__ inline void load_query_rows(int8_t* qs, int qstride, const int* s_q, 
     }
 }
 
+typedef const __attribute__((address_space(1))) void* gptr;
+typedef __attribute__((address_space(3))) void* lptr;
+
+// The int8 query rows of an item straight to LDS (no registers on the way; 16
+// bytes per lane and instruction), row qi at qs + qi * dp.  The 16-byte chunks
+// of a row stand in an order that depends on the row, chunk c at slot
+// c ^ (qi & 7) (c ^ (qi & 3) in a last group of four), so that the 16-byte
+// reads of one chunk of 32 rows cover all LDS banks although the rows have no
+// padding (the destination of these loads is contiguous).  Rows past mq take
+// those of query mq - 1: no estimate of theirs is kept.
+__device__ inline int row_swizzle(int c, int nch, int qi) { return c ^ (qi & ((c | 7) < nch ? 7 : 3)); }
+
+template <int NQT, bool LO>
+__device__ inline void rows_to_lds(int8_t* qs, const int* s_q, const int8_t* __restrict__ qint, int dp, int mq,
+                                   int lane, int wid, const int8_t* __restrict__ qlo)
+{
+    const int nch = dp >> 4;                       // 16-byte chunks per row, a multiple of 4
+    const float rnch = 1.0f / (float)nch;          // u / nch below is exact: u < 2^16, gap >= 0.5/nch
+    const int units = kQT * NQT * nch;             // a multiple of 128
+    for (int ub = wid * 64; ub < units; ub += kThreads) {
+        const int u = ub + lane;
+        const int qi = (int)(((float)u + 0.5f) * rnch);
+        const int c = row_swizzle(u - qi * nch, nch, qi);
+        const int qq = min(LO && qi >= kQT ? qi - kQT : qi, mq - 1);
+        const int8_t* src = (LO && qi >= kQT ? qlo : qint) + (int64_t)s_q[qq] * dp + 16 * c;
+        __builtin_amdgcn_global_load_lds((gptr)src, (lptr)(qs + 16 * ub), 16, 0, 0);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Pass B: items of 32*NQT queries; each wave step is 64 vectors (two code
 // tiles) x 32*NQT queries, so every unpacked code fragment feeds 2*NQT MFMAs
@@ -287,70 +323,158 @@ __global__ __launch_bounds__(kThreads, 2) void scanB_kernel(
     constexpr int QPI = kQT * NQT;
     extern __shared__ __align__(16) char smem[];
     __shared__ float s_s2[QPI], s_hd[QPI];
-    __shared__ int s_ss[QPI], s_slot[QPI], s_q[QPI], s_cnt[QPI], s_base[QPI];
+    __shared__ int s_ss[QPI], s_ssl[LO ? QPI : 1], s_slot[DENSE ? QPI : 1], s_q[2][QPI], s_cnt[QPI];
     __shared__ float s_be[QPI][kCapB];
     __shared__ int s_bi[QPI][kCapB];
     __shared__ unsigned s_tau[QPI];
     __shared__ float2 s_fac[kVch + 64];      // + NaN padding up to the group end
     __shared__ int s_id[kVch + 64];          // ids of the item's members (no global load in the epilogue)
-    __shared__ int s_item[5];
+    // of the next item: its number, queries, members, first member and first tile (64 bits each)
+    __shared__ int s_item[3];
+    __shared__ int64_t s_at[2];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: scalar
     const int n_items = item_off[nlist];
-    // Items are taken from a shared counter until it passes n_items; the id of
-    // the next item is fetched while the current one is scanned.
-    if (tid == 0) s_item[4] = atomicAdd(work, 1);
-    __syncthreads();
-    for (;;) {
-    const int item = s_item[4];
-    if (item >= n_items) break;
-    if (tid == 0) {
-        const int4 d = desc[item];
-        s_item[0] = d.x; s_item[1] = d.y; s_item[2] = d.z; s_item[3] = d.w;
-    }
-    if (tid < QPI) s_cnt[tid] = 0;
-    __syncthreads();
-    if (tid == 0) s_item[4] = atomicAdd(work, 1);  // read again only after the item's last barrier
-    const int l = s_item[0], p0 = s_item[1], mq = s_item[2], v0 = s_item[3];
+    if (n_items == 0) return;                    // a rescan without overflowed queries
     int8_t* qs = (int8_t*)smem;
-    const int qstride = dp + 16;
-    load_query_scalars(s_s2, s_hd, s_ss, s_slot, s_q, s_tau, tau_key, qa, pair_q + p0, pair_slot + p0, mq, tid);
-    {   // factors and ids of the item's members, all loads of a thread in
-        // flight at once; past the end NaN, which never passes
-        constexpr int KF = (kVch + 64 + kThreads - 1) / kThreads;
-        const int64_t fb = list_off[l] + v0;
-        const int nf = min((int)(list_off[l + 1] - list_off[l]) - v0, dense ? kDenseV : kVch);
-        const int nfp = (nf + 63) & ~63;
+    // Items are taken from a shared counter until it passes n_items.  What the
+    // next item needs is fetched while the current one is scanned, in three
+    // dependent steps of wave 0 (the wave with the fewest tiles): its number
+    // (before the scan), its descriptor (before the last group's products) and
+    // the queries of its pairs (before the last group's epilogue).  After the
+    // item's last barrier everything else is read at once: the int8 query rows,
+    // the members' factors and ids, the per-query terms, the first codes and
+    // the positions in the candidate buffers of the staged survivors of the
+    // item just ended, so that an item costs one memory latency beside its scan.
+    // (The steps keep their values in vector registers, written in place, so
+    // that none of them waits for its load.)
+    int nid = 0, ndv = 0;
+    int nq_ = 0, nslot_ = 0, nmq = 0, nmem = 0;
+    int64_t nfirst = 0, ntile0 = 0;
+    auto fetch_id = [&]() { if (lane == 0) nid = atomicAdd(work + lane, 1); };
+    auto fetch_desc = [&]() {                    // one component per lane
+        nid = __builtin_amdgcn_readfirstlane(nid);
+        if (nid < n_items) ndv = ((const int*)desc)[(int64_t)4 * nid + (lane & 3)];
+    };
+    auto fetch_pairs = [&]() {
+        if (nid >= n_items) return;
+        const int l = __builtin_amdgcn_readlane(ndv, 0), np0 = __builtin_amdgcn_readlane(ndv, 1);
+        const int nv0 = __builtin_amdgcn_readlane(ndv, 3);
+        nmq = __builtin_amdgcn_readlane(ndv, 2);
+        if (lane < nmq) { nslot_ = pair_slot[np0 + lane]; nq_ = pair_q[np0 + lane]; }
+        // members [v0, v0 + nmem) of list l (v0 is a multiple of 64: whole tile pairs)
+        nfirst = list_off[l] + nv0;
+        nmem = min((int)(list_off[l + 1] - nfirst), dense ? kDenseV : kVch);
+        ntile0 = tile_off[l] + (nv0 >> 5);
+    };
+    auto publish = [&](int par) {
+        if (lane < QPI) s_q[par][lane] = nq_;
+        if (lane == 0) { s_item[0] = nid; s_item[1] = nmq; s_item[2] = nmem; s_at[0] = nfirst; s_at[1] = ntile0; }
+    };
+    if (tid < QPI) s_cnt[tid] = 0;
+    if (wid == 0) { fetch_id(); fetch_desc(); fetch_pairs(); publish(0); }
+    __syncthreads();
+    int par = 0, mq_done = 0;                    // the parity of s_q / s_slot; queries of the item just ended
+    for (;; par ^= 1) {
+    const int item = __builtin_amdgcn_readfirstlane(s_item[0]);
+    const bool more = item < n_items;
+    const int mq = more ? __builtin_amdgcn_readfirstlane(s_item[1]) : 0;
+    const int nl = more ? __builtin_amdgcn_readfirstlane(s_item[2]) : 0;
+    const int64_t fb = uniform64(s_at[0]), tbase = uniform64(s_at[1]);
+    const int nkb = dp / 64;
+    const int64_t tile_bytes = (int64_t)4 * dp * BITS;
+    const int ntile = (nl + 31) >> 5;
+    // Wave wid takes the tiles [ta, tb) of the item (a contiguous quarter,
+    // so the waves differ by at most one tile) and walks them in groups of
+    // two tiles as one sequence of K-steps (group, kb); a group with one tile
+    // (the last of an odd range) skips the second tile's unpacking and
+    // MFMAs behind a wave-uniform branch.
+    // The packed codes of step s + PD are loaded while step s runs: a ring
+    // of PD slots of raw words in registers.  PD divides nkb, so the steps come
+    // in blocks of PD within one group, and a block loads the words of the next
+    // one; the last block of the item loads nothing.  A slot is refilled only
+    // after its unpacking (the scheduling barrier): loads moved above it would
+    // need registers of their own, and the copies of those back into the ring
+    // would wait for every load in flight, once per block.
+    const int ta = (wid * ntile) >> 2, tb = ((wid + 1) * ntile) >> 2;
+    const int ngw = (tb - ta + 1) >> 1;
+    const int total = ngw * nkb;
+    uint32_t ring[PD][2 * BITS];
+    const uint8_t* gp0 = codes + (tbase + ta) * tile_bytes;     // the group's first tile
+    // one block's words from p0 (second tile at p0 + d1, d1 = 0 for a group of one tile)
+    auto load_slot = [&](int p, const uint8_t* p0, int64_t d1) {
+        load_raw<BITS>(p0 + 256 * BITS * p, lane, ring[p]);
+        load_raw<BITS>(p0 + d1 + 256 * BITS * p, lane, ring[p] + BITS);
+    };
+    const int fqi = tid >> 2, fsub = tid & 3;    // the four threads of a staged query
+    int fm = 0, fbase = 0, fq = 0;
+    if (!dense && fqi < mq_done) {
+        fm = min(s_cnt[fqi], kCapB);
+        fq = s_q[par ^ 1][fqi];
+        if (fsub == 0 && fm > 0) fbase = atomicAdd(&gcnt[fq], fm);
+    }
+    if (more) {
+        rows_to_lds<NQT, LO>(qs, s_q[par], qa.qint, dp, mq, lane, wid, qa.qlo);
+        float t_s2 = 0.0f, t_hd = 0.0f;
+        int t_ss = 0, t_ssl = 0;
+        unsigned t_tau = 0;
+        if (tid < mq) {                          // per-query terms of the item's pairs (wave 0 holds them)
+            const int q = nq_;
+            t_s2 = qa.sdist[nslot_];
+            t_hd = qa.qhd[q];
+            t_ss = qa.qss[q];
+            if constexpr (LO) t_ssl = qa.qss_lo[q];
+            if constexpr (!dense) t_tau = tau_key[q];
+        }
+        // factors and ids of the item's members; past the end NaN, which never passes
+        constexpr int KF = ((dense ? kDenseV : kVch) + kThreads - 1) / kThreads;
+        const int nfp = (nl + 63) & ~63;
         float2 fv[KF];
         int iv[KF];
 #pragma unroll
         for (int k = 0; k < KF; ++k) {
             const int t = tid + k * kThreads;
-            const bool in = t < nf;
+            const bool in = t < nl;
             fv[k] = in ? fac[fb + t] : make_float2(__builtin_nanf(""), 0.0f);
             iv[k] = in ? (int)ids[fb + t] : -1;
+        }
+        if (total > 0) {                         // the first codes, too, arrive meanwhile
+#pragma unroll
+            for (int p = 0; p < PD; ++p) load_slot(p, gp0, ta + 1 < tb ? tile_bytes : 0);
         }
 #pragma unroll
         for (int k = 0; k < KF; ++k) {
             const int t = tid + k * kThreads;
             if (t < nfp) { s_fac[t] = fv[k]; s_id[t] = iv[k]; }
         }
+        if (tid < mq) {
+            s_s2[tid] = fmaxf(t_s2, qa.s2_floor);   // L2: the probe's expanded form may round below 0
+            s_hd[tid] = t_hd; s_ss[tid] = t_ss; s_tau[tid] = t_tau;
+            if constexpr (LO) s_ssl[tid] = t_ssl;
+            if constexpr (dense) s_slot[tid] = nslot_;
+        }
     }
+    if constexpr (!dense) {                      // the staged survivors to their queries' candidate buffers
+        fbase = __shfl(fbase, lane & ~3);
+        for (int e = fsub; e < fm; e += 4) {
+            if (fbase + e < kCapQ) {
+                gbuf_e[(int64_t)fq * kCapQ + fbase + e] = s_be[fqi][e];
+                gbuf_i[(int64_t)fq * kCapQ + fbase + e] = s_bi[fqi][e];
+            }
+        }
+        if (fqi < mq_done && fsub == 0) s_cnt[fqi] = 0;
+    }
+    if (!more) break;
     __syncthreads();
-    load_query_rows<NQT, LO>(qs, qstride, s_q, qa.qint, dp, mq, tid, qa.qlo);
-    __syncthreads();
+    if (wid == 0) fetch_id();
 
-    const int nkb = dp / 64;
     // B fragment of lane (h = lane/32, j = lane%32) for query tile qt: query
-    // qt*32 + j, bytes 16h.. of each 32-dim block
-    const int8_t* qrow = qs + (lane & 31) * qstride + 16 * (lane >> 5);
-    const int64_t tile_bytes = (int64_t)4 * dp * BITS;
-    // members [v0, v0 + nl) of list l (v0 is a multiple of 64: whole tile pairs)
-    const int nl = min((int)(list_off[l + 1] - list_off[l]) - v0, dense ? kDenseV : kVch);
-    const int ntile = (nl + 31) >> 5;
-    const int64_t tbase = tile_off[l] + (v0 >> 5);
-    const int j = lane & 31;
+    // qt*32 + j, bytes 16h.. of each 32-dim block (chunks 4 kb + h and
+    // 4 kb + 2 + h of K-block kb, in the row's order)
+    const int j = lane & 31, h = lane >> 5;
+    const int8_t* qrow = qs + j * dp;
+    const int nch = dp >> 4;
     // Columns without a query (qi >= mq) have no LDS terms: they take zeros
     // and are excluded from the pass test by qok, not by their estimate.
     float qs2[NQT], qhd[NQT], qtau[NQT];
@@ -378,56 +502,23 @@ __global__ __launch_bounds__(kThreads, 2) void scanB_kernel(
         cAQ[qt] = qok[qt] ? aq + (fabsf(qtau[qt]) + fabsf(qs2[qt])) * 0x1p-20f : -__builtin_huge_valf();
     }
     if constexpr (LO)
-        epi_consts2<BITS>(qhd[0], qss[0], qok[0] ? qa.qss_lo[s_q[j]] : 0, cH2[0], cH2L, cHC[0]);
+        epi_consts2<BITS>(qhd[0], qss[0], qok[0] ? s_ssl[j] : 0, cH2[0], cH2L, cHC[0]);
 
-    // Wave wid takes the tiles [ta, tb) of the item (a contiguous quarter,
-    // so the waves differ by at most one tile) and walks them in groups of
-    // two tiles as one sequence of K-steps (group, kb); a group with one tile
-    // (the last of an odd range) skips the second tile's unpacking and
-    // MFMAs behind a wave-uniform branch.
-    // The packed codes of step s + PD are loaded while step s runs: a ring
-    // of PD slots of raw words in registers, unrolled by PD so that each slot
-    // is consumed and refilled in place (no copy of a register whose load is
-    // in flight).  PD divides nkb, so a group always ends with the last slot.
-    // Past the end the last step is loaded again, so no load is conditional.
-    const int ta = (wid * ntile) >> 2, tb = ((wid + 1) * ntile) >> 2;
-    const int ngw = (tb - ta + 1) >> 1;
-    const int total = ngw * nkb;
     if (total > 0) {
-        uint32_t ring[PD][2 * BITS];
-        // next step to load: group tile t0 at p0 (second tile p0 + d1, or p0
-        // itself for a single-tile group), K-block offset koff
-        int t0 = ta, pleft = total;
-        const uint8_t* p0 = codes + (tbase + t0) * tile_bytes;
-        int64_t d1 = (t0 + 1 < tb) ? tile_bytes : 0;
-        int64_t koff = 0;
-        auto load_step = [&](uint32_t* d) {
-            load_raw<BITS>(p0 + koff, lane, d);
-            load_raw<BITS>(p0 + d1 + koff, lane, d + BITS);
-            if (pleft > 1) {
-                --pleft;
-                koff += 256 * BITS;
-                if (koff == tile_bytes) {
-                    koff = 0;
-                    t0 += 2;
-                    p0 += 2 * tile_bytes;
-                    d1 = (t0 + 1 < tb) ? tile_bytes : 0;
-                }
-            }
-        };
-#pragma unroll
-        for (int p = 0; p < PD; ++p) load_step(ring[p]);
         // query fragments of K-block kb (they do not depend on the group):
         // those of the next K-block are read from LDS while this one's MFMAs run
         auto read_b = [&](int kb, v4i (&b)[NQT][2]) {
+            const int sw = j & ((4 * kb | 7) < nch ? 7 : 3);
+            const int8_t* r0 = qrow + 16 * ((4 * kb + h) ^ sw);
+            const int8_t* r1 = qrow + 16 * ((4 * kb + 2 + h) ^ sw);
 #pragma unroll
             for (int qt = 0; qt < NQT; ++qt) {
-                b[qt][0] = *(const v4i*)(qrow + qt * kQT * qstride + 64 * kb);
-                b[qt][1] = *(const v4i*)(qrow + qt * kQT * qstride + 64 * kb + 32);
+                b[qt][0] = *(const v4i*)(r0 + qt * kQT * dp);
+                b[qt][1] = *(const v4i*)(r1 + qt * kQT * dp);
             }
         };
-        v4i bq[NQT][2];
-        read_b(0, bq);
+        v4i bq[2][NQT][2];
+        read_b(0, bq[0]);
         v16i acc[2][NQT];
         // code x query products of a K-block; the first bound takes the
         // transposed product (rows queries, columns members) so that its
@@ -437,45 +528,55 @@ __global__ __launch_bounds__(kThreads, 2) void scanB_kernel(
             if constexpr (DENSE) return __builtin_amdgcn_mfma_i32_32x32x32_i8(b, a, c, 0, 0, 0);
             else return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
         };
-        // the nkb K-steps of one group, for a group of two tiles or of one
-        // (the width is a compile-time constant of each loop body)
-        auto run_group = [&](auto two_c) {
-            constexpr bool TWO = decltype(two_c)::value;
+        for (int gi = 0; gi < ngw; ++gi) {
+            const int gt0 = ta + 2 * gi;                // first tile of the group
+            const bool two = gt0 + 1 < tb;
+            const bool fetch = wid == 0 && gi + 1 == ngw;
+            if (fetch) fetch_desc();
 #pragma unroll
-            for (int a = 0; a < (TWO ? 2 : 1); ++a)
+            for (int a = 0; a < 2; ++a)
 #pragma unroll
                 for (int qt = 0; qt < NQT; ++qt)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) acc[a][qt][r] = 0;
+            // the next block's words: of this group, of the next one, or (after
+            // the last block) the same block's again
+            const uint8_t* pk = gp0;
+            if (gi + 1 < ngw) gp0 += 2 * tile_bytes;
+            const int64_t dk = two ? tile_bytes : 0;
             for (int kb0 = 0; kb0 < nkb; kb0 += PD) {
+                const bool in = kb0 + PD < nkb;
+                pk += 256 * BITS * PD;
+                const uint8_t* pn = in ? pk : gi + 1 < ngw ? gp0 : pk - 256 * BITS * PD;
+                const int64_t dn = in || gi + 1 == ngw ? dk : gt0 + 3 < tb ? tile_bytes : 0;
 #pragma unroll
                 for (int p = 0; p < PD; ++p) {
                     v4i a00, a01, a10, a11;
                     unpack_raw<BITS>(ring[p], a00, a01);
-                    if constexpr (TWO) unpack_raw<BITS>(ring[p] + BITS, a10, a11);
-                    load_step(ring[p]);
+                    unpack_raw<BITS>(ring[p] + BITS, a10, a11);
+                    asm volatile("" : "+v"(a00), "+v"(a01), "+v"(a10), "+v"(a11));
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_slot(p, pn, dn);
                     const int kb = kb0 + p;
-                    v4i bn[NQT][2];
-                    read_b(kb + 1 < nkb ? kb + 1 : 0, bn);
+                    v4i (&b)[NQT][2] = bq[p & 1];
+                    read_b(kb + 1 < nkb ? kb + 1 : 0, bq[(p & 1) ^ 1]);
 #pragma unroll
-                    for (int qt = 0; qt < NQT; ++qt) {
-                        acc[0][qt] = mm(a00, bq[qt][0], acc[0][qt]);
-                        if constexpr (TWO) acc[1][qt] = mm(a10, bq[qt][0], acc[1][qt]);
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int qt = 0; qt < NQT; ++qt) acc[0][qt] = mm(t ? a01 : a00, b[qt][t], acc[0][qt]);
+                    if (two) {
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+#pragma unroll
+                            for (int qt = 0; qt < NQT; ++qt) acc[1][qt] = mm(t ? a11 : a10, b[qt][t], acc[1][qt]);
                     }
+                }
+                if constexpr (PD & 1) {
 #pragma unroll
-                    for (int qt = 0; qt < NQT; ++qt) {
-                        acc[0][qt] = mm(a01, bq[qt][1], acc[0][qt]);
-                        if constexpr (TWO) acc[1][qt] = mm(a11, bq[qt][1], acc[1][qt]);
-                    }
-#pragma unroll
-                    for (int qt = 0; qt < NQT; ++qt) { bq[qt][0] = bn[qt][0]; bq[qt][1] = bn[qt][1]; }
+                    for (int qt = 0; qt < NQT; ++qt) { bq[0][qt][0] = bq[1][qt][0]; bq[0][qt][1] = bq[1][qt][1]; }
                 }
             }
-        };
-        for (int gi = 0; gi < ngw; ++gi) {
-            const int gt0 = ta + 2 * gi;                // first tile of the group
-            if (gt0 + 1 < tb) run_group(std::true_type{});
-            else run_group(std::false_type{});
+            if (fetch) fetch_pairs();
             // epilogue of group g: estimates, bound test, survivors to the stage.
             // The tile's 16 factor pairs are read from LDS before any is used,
             // and nothing here touches global memory except the rare overflow
@@ -503,14 +604,15 @@ __global__ __launch_bounds__(kThreads, 2) void scanB_kernel(
                                 float h2, hc, e;
                                 if constexpr (LO) {
                                     float h2l;
-                                    epi_consts2<BITS>(s_hd[qi], s_ss[qi], qa.qss_lo[s_q[qi]], h2, h2l, hc);
+                                    epi_consts2<BITS>(s_hd[qi], s_ss[qi], s_ssl[qi], h2, h2l, hc);
                                     e = epi_e2(f, acc[a][0][r], acc[a][1][r], h2, h2l, hc);
                                 } else {
                                     epi_consts<BITS>(s_hd[qi], s_ss[qi], h2, hc);
                                     e = epi_e(f, acc[a][qt][r], h2, hc);
                                 }
-                                const int q = s_q[qi];
-                                const int64_t sl = (int64_t)q * kCapQ + (int64_t)(s_slot[qi] - q * nprobe) * kDenseV;
+                                const int q = s_q[par][qi];
+                                const int64_t sl =
+                                    (int64_t)q * kCapQ + (int64_t)(s_slot[qi] - q * nprobe) * kDenseV;
                                 gbuf_e[sl + v] = e + s_s2[qi];
                                 gbuf_i[sl + v] = id;
                             }
@@ -518,75 +620,61 @@ __global__ __launch_bounds__(kThreads, 2) void scanB_kernel(
                     }
                     continue;
                 }
+                // all of the tile's estimates and bound tests first, then one
+                // place for a lane's survivors of a query in the stage (an
+                // atomic for each estimate that passes would wait for the LDS
+                // once per row)
                 float2 fr[16];
 #pragma unroll
                 for (int r = 0; r < 16; ++r) fr[r] = s_fac[tt * 32 + out_row(lane, r)];   // NaN past the end
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int v = tt * 32 + out_row(lane, r);
-                    const float2 f = fr[r];
-                    float e[NQT];
-                    bool pass[NQT], anyp = false;
-                    if constexpr (LO) {                     // one estimate from the two planes
-                        e[0] = epi_e2(f, acc[a][0][r], acc[a][1][r], cH2[0], cH2L, cHC[0]);
-                        pass[0] = e[0] <= cAQ[0];
-                        pass[1] = false;
-                        e[1] = 0.0f;
-                        anyp = pass[0];
-                    } else {
+                for (int qt = 0; qt < (LO ? 1 : NQT); ++qt) {
+                    float e[16];
+                    bool pass[16];
+                    int n = 0;
 #pragma unroll
-                        for (int qt = 0; qt < NQT; ++qt) {
-                            e[qt] = epi_e(f, acc[a][qt][r], cH2[qt], cHC[qt]);
-                            pass[qt] = e[qt] <= cAQ[qt];
-                            anyp = anyp || pass[qt];
-                        }
+                    for (int r = 0; r < 16; ++r) {
+                        if constexpr (LO)                   // one estimate from the two planes
+                            e[r] = epi_e2(fr[r], acc[a][0][r], acc[a][1][r], cH2[0], cH2L, cHC[0]);
+                        else
+                            e[r] = epi_e(fr[r], acc[a][qt][r], cH2[qt], cHC[qt]);
+                        pass[r] = e[r] <= cAQ[qt];
+                        n += pass[r] ? 1 : 0;
                     }
-                    if (!__any(anyp)) continue;
+                    if (!__any(n > 0)) continue;
+                    const int qi = qt * kQT + j;
+                    int pos = n > 0 ? atomicAdd(&s_cnt[qi], n) : 0;
+                    int q = 0, gpos = 0;                    // stage full: straight to HBM
+                    if (n > 0 && pos + n > kCapB) {
+                        q = s_q[par][qi];
+                        const int nx = min(n, pos + n - kCapB);
+                        gpos = atomicAdd(&gcnt[q], nx) - (pos + n - nx);
+                    }
 #pragma unroll
-                    for (int qt = 0; qt < (LO ? 1 : NQT); ++qt) {
-                        if (!pass[qt]) continue;
-                        const float est = e[qt] + qs2[qt];
-                        const int qi = qt * kQT + j;
-                        const int id = s_id[v];
-                        const int pos = atomicAdd(&s_cnt[qi], 1);
+                    for (int r = 0; r < 16; ++r) {
+                        if (!pass[r]) continue;
+                        const float est = e[r] + qs2[qt];
+                        const int id = s_id[tt * 32 + out_row(lane, r)];
                         if (pos < kCapB) {
                             s_be[qi][pos] = est; s_bi[qi][pos] = id;
-                        } else {                            // stage full: straight to HBM
-                            const int q = s_q[qi];
-                            const int gp = atomicAdd(&gcnt[q], 1);
-                            if (gp < kCapQ) {
-                                gbuf_e[(int64_t)q * kCapQ + gp] = est;
-                                gbuf_i[(int64_t)q * kCapQ + gp] = id;
-                            }
+                        } else if (gpos + pos < kCapQ) {
+                            gbuf_e[(int64_t)q * kCapQ + gpos + pos] = est;
+                            gbuf_i[(int64_t)q * kCapQ + gpos + pos] = id;
                         }
+                        ++pos;
                     }
                 }
             }
         }
+    } else if (wid == 0) {
+        fetch_desc();
+        fetch_pairs();
     }
+    if (wid == 0) publish(par ^ 1);
+    mq_done = mq;
     __syncthreads();
-    // flush the LDS stage to the query's candidate buffer
-    const int qi = tid >> 2, sub = tid & 3;
-    if (qi < mq && sub == 0) {
-        const int m = min(s_cnt[qi], kCapB);
-        s_base[qi] = (m > 0) ? atomicAdd(&gcnt[s_q[qi]], m) : 0;
-    }
-    __syncthreads();
-    if (qi < mq) {
-        const int q = s_q[qi];
-        const int m = min(s_cnt[qi], kCapB);
-        const int base = s_base[qi];
-        for (int e = sub; e < m; e += 4) {
-            if (base + e < kCapQ) {
-                gbuf_e[(int64_t)q * kCapQ + base + e] = s_be[qi][e];
-                gbuf_i[(int64_t)q * kCapQ + base + e] = s_bi[qi][e];
-            }
-        }
-    }
-    __syncthreads();                               // LDS of this item is free; s_item[4] is the next id
     }
 }
-
 
 // ---------------------------------------------------------------------------
 // Two-stage pass B (Sec. 4.2, most significant bits first).  For a group of
@@ -2045,7 +2133,7 @@ template <int BITS, int NQT, int PD, bool DENSE, bool LO>
 hipError_t launchB_d(const Index* ix, const ScanArgs& a, const BArgs& b, hipStream_t st)
 {
     const void* kern = (const void*)scanB_kernel<BITS, NQT, PD, DENSE, LO>;
-    const size_t sm = (size_t)(ix->dc + 16) * kQT * NQT;
+    const size_t sm = (size_t)ix->dc * kQT * NQT;
     if (sm > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
         if (e != hipSuccess) return e;
