@@ -958,7 +958,7 @@ __global__ __launch_bounds__(kThreads, 2) void scan2_kernel(
 //           estimates of distinct members, so still a valid bound).
 // ---------------------------------------------------------------------------
 constexpr int kSelQ = 4;               // queries (waves) per block
-constexpr int kSelB = 8;               // entries per lane loaded together (512 per wave)
+constexpr int kSelB = 16;              // entries per lane loaded together (1024 per wave: a first bound's slots)
 
 // LDS written by some lanes of a wave and read by others: wait for the
 // wave's LDS operations and keep the compiler from moving accesses across
@@ -1476,11 +1476,15 @@ __device__ __attribute__((always_inline)) inline unsigned long long block_keep(
 //    candidate buffer still overflowed; writes the sorted result;
 //  * small batches (slices = S > 0, ovf and gate null): workgroup (q, s)
 //    takes the s-th of S equal parts of query q's member tiles (over all its
-//    probed lists, in probe order) and appends its top-kk
-//    (unsorted) to the query's candidate buffer, whose count starts at 0
-//    (at most S kk <= kCapQ entries, all distinct members), for the final
-//    select; a search of a few queries then runs in a handful of launches.
-// Grid-stride over (query, slice).  Dynamic LDS: kCapE keys, the tile prefix
+//    probed lists, in probe order) and appends a set that holds its top-kk
+//    (unsorted, at most kCapQ / S >= kk entries, all distinct members) to the
+//    query's candidate buffer, whose count starts at 0, for the final select; a
+//    search of a few queries then runs in a handful of launches.  The set is
+//    the keys at or under the kk-th smallest of one wave's lane minima (the
+//    rule of buf_select_kernel) for kk <= 64, when they fit; else every key, or
+//    the exact top-kk when those are too many (a radix select of eight passes:
+//    about 5 us of a slice that is otherwise a few us long).
+// Grid-stride over (query, slice).  Dynamic LDS: cap_e keys, the tile prefix
 // over the probes (nprobe + 1 ints, rounded up to 16 bytes) and the query's
 // int8 rows (dp bytes per plane).  redo counts the probed pairs of the
 // fallback's queries (diagnostics).
@@ -1488,7 +1492,7 @@ template <int BITS, bool LO>
 __global__ __launch_bounds__(256) void exact_kernel(
     const uint8_t* __restrict__ codes, const int64_t* __restrict__ tile_off, const int64_t* __restrict__ list_off,
     const float2* __restrict__ fac, const int64_t* __restrict__ ids, int dp, QArgs qa,
-    const int32_t* __restrict__ probes, int64_t nq, int nprobe, int nlist, int kk,
+    const int32_t* __restrict__ probes, int64_t nq, int nprobe, int nlist, int kk, int cap_e,
     const int32_t* __restrict__ ovf, const int32_t* __restrict__ gate, int32_t* __restrict__ redo,
     int64_t* __restrict__ out_ids, float* __restrict__ out_est, int slices, int32_t* __restrict__ gcnt,
     float* __restrict__ gbuf_e, int32_t* __restrict__ gbuf_i)
@@ -1497,10 +1501,10 @@ __global__ __launch_bounds__(256) void exact_kernel(
     const int S = slices > 0 ? slices : 1;
     extern __shared__ __align__(16) char smem[];
     unsigned long long* keys = (unsigned long long*)smem;
-    int* tpref = (int*)(smem + sizeof(unsigned long long) * kCapE);
+    int* tpref = (int*)(smem + sizeof(unsigned long long) * cap_e);
     int8_t* qs = (int8_t*)(tpref + ((nprobe + 4) & ~3));
     __shared__ unsigned hist[256], s_w[4], s_bc[2];
-    __shared__ int s_cnt;
+    __shared__ int s_cnt, s_done;
     __shared__ unsigned long long s_T;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int nkb = dp / 64;
@@ -1566,6 +1570,12 @@ __global__ __launch_bounds__(256) void exact_kernel(
                 const int64_t lb = list_off[l];
                 const int nl = (int)(list_off[l + 1] - lb);
                 const uint8_t* tp = codes + (tile_off[l] + tt) * tile_bytes;
+                // this lane's member (below); its factors and id arrive with the codes
+                const int j = lane & 31, v = tt * 32 + out_row(lane, j & 15);
+                const bool mine = j < 16 && v < nl;
+                float2 f = make_float2(0.0f, 0.0f);
+                int id = 0;
+                if (mine) { f = fac[lb + v]; id = (int)ids[lb + v]; }
                 v16i acc;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[r] = 0;
@@ -1590,25 +1600,19 @@ __global__ __launch_bounds__(256) void exact_kernel(
                 }
                 // lane (h, j < 16) takes output row out_row(lane, j): the 32
                 // lanes cover the tile's 32 members once
-                const int j = lane & 31;
                 int a = acc[0];
 #pragma unroll
                 for (int r = 1; r < 16; ++r) a = (r == (j & 15)) ? acc[r] : a;
                 // LO: lane j + 16 holds the low plane's product of the same row
                 const int alo = LO ? __shfl_down(a, 16) : 0;
-                if (j < 16) {
-                    const int v = tt * 32 + out_row(lane, j);
-                    if (v < nl) {
-                        const float est = (LO ? epi_e2(fac[lb + v], a, alo, h2, h2l, hc)
-                                              : epi_e(fac[lb + v], a, h2, hc)) + s2;
-                        const unsigned long long key =
-                            ((unsigned long long)f2key(est) << 32) | (unsigned)(int)ids[lb + v];
-                        if (key < T) keys[atomicAdd(&s_cnt, 1)] = key;
-                    }
+                if (mine) {
+                    const float est = (LO ? epi_e2(f, a, alo, h2, h2l, hc) : epi_e(f, a, h2, hc)) + s2;
+                    const unsigned long long key = ((unsigned long long)f2key(est) << 32) | (unsigned)id;
+                    if (key < T) keys[atomicAdd(&s_cnt, 1)] = key;
                 }
             }
             __syncthreads();
-            if (s_cnt > kCapE - 4 * 32) {        // room for the next step's 128 candidates
+            if (s_cnt > cap_e - 4 * 32) {        // room for the next step's 128 candidates
                 const unsigned long long kth = block_keep(keys, s_cnt, kk, hist, s_w, s_bc);
                 if (tid == 0) { s_cnt = kk; s_T = kth; }
                 __syncthreads();
@@ -1616,7 +1620,39 @@ __global__ __launch_bounds__(256) void exact_kernel(
         }
         const int c = s_cnt;
         int m = c;
-        if (c > kk) {
+        if (slices > 0 && c > kk && c <= 1024 && kk <= 64) {
+            if (wid == 0) {
+                unsigned long long mn = ~0ull;
+                for (int t = lane; t < c; t += 64) mn = min(mn, keys[t]);
+                mn = wave_sort_u64(mn, lane);
+                const unsigned thi = (unsigned)__shfl((int)(unsigned)(mn >> 32), kk - 1);
+                const unsigned long long T =
+                    ((unsigned long long)thi << 32) | (unsigned)__shfl((int)(unsigned)mn, kk - 1);
+                int n = 0;
+                for (int b = 0; b < c; b += 64) n += __popcll(__ballot(b + lane < c && keys[b + lane] <= T));
+                const bool fits = n <= kCapQ / S;
+                if (fits) {
+                    int run = 0;
+                    if (lane == 0) run = atomicAdd(&gcnt[q], n);
+                    run = __builtin_amdgcn_readfirstlane(run);
+                    for (int b = 0; b < c; b += 64) {
+                        const unsigned long long k = b + lane < c ? keys[b + lane] : ~0ull;
+                        const bool in = b + lane < c && k <= T;
+                        const unsigned long long bal = __ballot(in);
+                        if (in) {
+                            const int64_t at = q * kCapQ + run + __popcll(bal & ((1ull << lane) - 1ull));
+                            gbuf_e[at] = key2f((unsigned)(k >> 32));
+                            gbuf_i[at] = (int32_t)(unsigned)(k & 0xFFFFFFFFull);
+                        }
+                        run += __popcll(bal);
+                    }
+                }
+                if (lane == 0) s_done = fits ? 1 : 0;
+            }
+            __syncthreads();
+            if (s_done) continue;                // read again only after a barrier of the next slice
+        }
+        if (c > (slices > 0 ? kCapQ / S : kk)) {
             block_keep(keys, c, kk, hist, s_w, s_bc);
             m = kk;
         }
@@ -1664,18 +1700,20 @@ __global__ __launch_bounds__(256) void exact_kernel(
 // even, clamp to +-127), delta/2 and the sum of the int8 values; one wave per query
 // (the first dp coordinates of each row of qrot, rows ld apart)
 // qlo (or null): the low plane, q_lo = rint((q' * inv - q_int) * 254), and its sums
+// zero (or null): nq counters to clear
 __global__ __launch_bounds__(256) void qprep_kernel(const float* __restrict__ qrot, int64_t nq, int dp, int ld,
                                                     int8_t* __restrict__ qint, float* __restrict__ qhd,
                                                     int32_t* __restrict__ qss, int8_t* __restrict__ qlo,
-                                                    int32_t* __restrict__ qss_lo)
+                                                    int32_t* __restrict__ qss_lo, int32_t* __restrict__ zero)
 {
     const int lane = threadIdx.x & 63;
     const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (q >= nq) return;
+    if (zero && lane == 0) zero[q] = 0;
     const float* qv = qrot + q * ld;
-    // rows of whole 256-float blocks, 16-byte aligned: four consecutive
-    // coordinates per lane and access (same arithmetic per coordinate)
-    const bool vec = (dp & 255) == 0 && (((uintptr_t)qv) & 15) == 0;
+    // rows that are 16-byte aligned: four consecutive coordinates per lane and
+    // access (same arithmetic per coordinate; dp is a multiple of 64)
+    const bool vec = (((uintptr_t)qv) & 15) == 0;
     float amax = 0.0f;
     if (vec) {
         for (int i = 4 * lane; i < dp; i += 256) {
@@ -2273,11 +2311,14 @@ hipError_t launch_exact_l(const Index* ix, const QArgs& qa, const int32_t* probe
                           const int32_t* ovf, const int32_t* gate, int32_t* redo, int64_t* oi, float* oe,
                           const ExactOut& xo, hipStream_t st)
 {
-    const size_t sm = sizeof(unsigned long long) * kCapE + sizeof(int) * ((nprobe + 4) & ~3) +
+    // a slice holds few keys, and more workgroups are resident with a smaller
+    // store (it is compacted when full: room for kk and a step's 128 is needed)
+    const int cap_e = xo.slices > 0 && kk <= 256 ? 1024 : kCapE;
+    const size_t sm = sizeof(unsigned long long) * cap_e + sizeof(int) * ((nprobe + 4) & ~3) +
                       (size_t)ix->dc * (LO ? 2 : 1);
     const unsigned grid = (unsigned)std::min<int64_t>(nq * std::max(xo.slices, 1), 4096);
     hipLaunchKernelGGL((exact_kernel<BITS, LO>), dim3(grid), dim3(256), sm, st, ix->codes, ix->tile_off,
-                       ix->list_off, ix->sfac, ix->ids, ix->dc, qa, probes, nq, nprobe, (int)ix->nlist, kk, ovf, gate,
+                       ix->list_off, ix->sfac, ix->ids, ix->dc, qa, probes, nq, nprobe, (int)ix->nlist, kk, cap_e, ovf, gate,
                        redo, oi, oe, xo.slices, xo.gcnt, xo.gbuf_e, xo.gbuf_i);
     return hipGetLastError();
 }
@@ -2499,9 +2540,24 @@ int run_scan(Index* ix, const float* qrot, int64_t qld, int64_t nq, const int32_
     const int qpiB = ix->qplanes == 2 ? kQT : scan_nqt(ix) * kQT;   // queries per item of the launched kernel
     const int pr = prof_begin(PK_SCAN, st);
     hipError_t e = hipSuccess;
+    // Small batches (at most ix->small_q queries): the pair-grouped pipeline
+    // (first bound, rounds, selects; about 35 launches) is set by its launch
+    // count, not by work.  Each query's probed lists are instead split over S
+    // workgroups that keep exact top-kk lists (exact_kernel, slice mode), and
+    // one final select merges them: the same exact top-kk by (est, id).
+    // With S below 16 (kk > 256 at nprobe >= 16) each workgroup would keep a
+    // long exact list over a large share of the probed members; such calls
+    // take the pipeline.
+    // Fewer than 512 workgroups in all leave compute units idle, so a query is
+    // then split into up to 32 parts also when it has fewer lists, as far as its
+    // buffer holds kk from each (one query, 16 lists of 200 members: 16 parts
+    // 64 us, 32 parts 56 us, 64 parts 59 us: the select reads more).
+    const int small_s = std::min(std::min(nprobe, kSmallS), std::max(1, kCapQ / kk));
+    const bool small = nq <= ix->small_q && small_s >= std::min(nprobe, 16);
+    const int slices = std::min((int)std::max<int64_t>(small_s, std::min<int64_t>(32, 512 / nq)), std::min(kSmallS, std::max(1, kCapQ / kk)));
     // queries to int8 once; ||s||^2 per pair from the probe distances, else computed
     hipLaunchKernelGGL(qprep_kernel, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, st, qrot, nq, dp, (int)qld, qint,
-                       qhd, qss, lo ? qlo : nullptr, lo ? qss_lo : nullptr);
+                       qhd, qss, lo ? qlo : nullptr, lo ? qss_lo : nullptr, small ? gcnt : nullptr);
     const float* sdist = pdist;
     const bool ip = ix->metric != ERQ_METRIC_L2;
     if (!sdist && P > 0) {
@@ -2515,20 +2571,10 @@ int run_scan(Index* ix, const float* qrot, int64_t qld, int64_t nq, const int32_
     }
     const QArgs qa{qint, qhd, qss, sdist, ip ? -__builtin_huge_valf() : 0.0f, lo ? qlo : nullptr,
                    lo ? qss_lo : nullptr};
-    // Small batches (at most ix->small_q queries): the pair-grouped pipeline
-    // (first bound, rounds, selects; about 35 launches) is set by its launch
-    // count, not by work.  Each query's probed lists are instead split over S
-    // workgroups that keep exact top-kk lists (exact_kernel, slice mode), and
-    // one final select merges them: the same exact top-kk by (est, id).
-    // With S below 16 (kk > 256 at nprobe >= 16) each workgroup would keep a
-    // long exact list over a large share of the probed members; such calls
-    // take the pipeline.
-    const int small_s = std::min(std::min(nprobe, kSmallS), std::max(1, kCapQ / kk));
-    if (nq <= ix->small_q && small_s >= std::min(nprobe, 16)) {
+    if (small) {
         const int pc = prof_begin(PK_SCAN_C, st);
-        zero(gcnt, nq);
         hipError_t e = launch_exact(ix, qa, probes, nq, nprobe, kk, nullptr, nullptr, nullptr, nullptr, nullptr, st,
-                                    ExactOut{small_s, gcnt, gbe, gbi});
+                                    ExactOut{slices, gcnt, gbe, gbi});
         if (e == hipSuccess) {
             const size_t sel_lds0 = (size_t)kSelQ * sel_slots(kk) * (sizeof(float) + sizeof(int));
             hipLaunchKernelGGL(buf_select_kernel<1>, dim3((unsigned)((nq + kSelQ - 1) / kSelQ)), dim3(256), sel_lds0,
