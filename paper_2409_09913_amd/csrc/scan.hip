@@ -1996,30 +1996,6 @@ __global__ __launch_bounds__(256) void pair_colsum_kernel(int32_t* __restrict__ 
     if (bq == 3) cnt[l] = run;
 }
 
-__global__ __launch_bounds__(1024) void pair_place_kernel(const int32_t* __restrict__ probes, int64_t np, int nprobe,
-                                                          int nlist, int rlo, int rhi,
-                                                          const int32_t* __restrict__ qmask,
-                                                          const int32_t* __restrict__ cnt2,
-                                                          const int32_t* __restrict__ off,
-                                                          int32_t* __restrict__ pq, int32_t* __restrict__ pslot,
-                                                          const int32_t* __restrict__ gate)
-{
-    if (gate && *gate == 0) return;
-    __shared__ int base[kHistMax];
-    const int b = blockIdx.x;
-    for (int l = threadIdx.x; l < nlist; l += blockDim.x) base[l] = off[l] + cnt2[(int64_t)b * nlist + l];
-    __syncthreads();
-    const int64_t chunk = (np + gridDim.x - 1) / gridDim.x;
-    const int64_t i0 = b * chunk, i1 = min(np, i0 + chunk);
-    for (int64_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
-        int l; int64_t q;
-        if (!pair_sel(probes, i, nprobe, nlist, rlo, rhi, qmask, &l, &q)) continue;
-        const int pos = atomicAdd(&base[l], 1);
-        pq[pos] = (int32_t)q;
-        pslot[pos] = (int32_t)i;
-    }
-}
-
 __device__ inline void list_scan(const int32_t* __restrict__ cnt, int nlist, const int32_t* __restrict__ list_order,
                                  const int64_t* __restrict__ list_off, int qpi, int vch, int vs,
                                  int32_t* __restrict__ pair_off, int32_t* __restrict__ item_off);
@@ -2119,6 +2095,40 @@ __global__ void item_desc_kernel(const int32_t* __restrict__ item_off, const int
     const int64_t item = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;   // empty build: item_off[nlist] == 0
     if (item >= cap || item >= item_off[nlist]) return;
     item_desc_one(item, item_off, list_order, list_off, pair_off, nlist, qpi, vch, vs, desc);
+}
+
+// The two steps that follow the list prefix and do not depend on each other,
+// in one launch (a launch of its own costs about 5 us in the stream): the first
+// kPairBlocks workgroups place the pairs, the others write the descriptors.
+__global__ __launch_bounds__(1024) void pair_place_kernel(const int32_t* __restrict__ probes, int64_t np, int nprobe,
+                                                          int nlist, int rlo, int rhi,
+                                                          const int32_t* __restrict__ cnt2,
+                                                          const int32_t* __restrict__ off,
+                                                          int32_t* __restrict__ pq, int32_t* __restrict__ pslot,
+                                                          const int32_t* __restrict__ item_off,
+                                                          const int32_t* __restrict__ list_order,
+                                                          const int64_t* __restrict__ list_off, int qpi, int vch,
+                                                          int vs, int64_t cap, int4* __restrict__ desc)
+{
+    __shared__ int base[kHistMax];
+    const int b = blockIdx.x;
+    if (b >= kPairBlocks) {
+        const int64_t item = (int64_t)(b - kPairBlocks) * blockDim.x + threadIdx.x;
+        if (item < cap && item < item_off[nlist])
+            item_desc_one(item, item_off, list_order, list_off, off, nlist, qpi, vch, vs, desc);
+        return;
+    }
+    for (int l = threadIdx.x; l < nlist; l += blockDim.x) base[l] = off[l] + cnt2[(int64_t)b * nlist + l];
+    __syncthreads();
+    const int64_t chunk = (np + kPairBlocks - 1) / kPairBlocks;
+    const int64_t i0 = b * chunk, i1 = min(np, i0 + chunk);
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
+        int l; int64_t q;
+        if (!pair_sel(probes, i, nprobe, nlist, rlo, rhi, nullptr, &l, &q)) continue;
+        const int pos = atomicAdd(&base[l], 1);
+        pq[pos] = (int32_t)q;
+        pslot[pos] = (int32_t)i;
+    }
 }
 
 // A gated pair build (the rescan of overflowed queries, the exact fallback)
@@ -2511,13 +2521,15 @@ int run_scan(Index* ix, const float* qrot, int64_t qld, int64_t nq, const int32_
         hipLaunchKernelGGL(pair_scan_kernel, dim3(1), dim3(1024), 0, st, cnt, (int)nlist, ix->list_order,
                            ix->list_off, qpi, vch, vs, poff, ioff, lds_sort ? gate : nullptr, work,
                            gate ? nullptr : anyf, gate ? nullptr : anyf2);
+        if (!reuse && lds_sort) {
+            hipLaunchKernelGGL(pair_place_kernel, dim3((unsigned)(kPairBlocks + (dcap + 1023) / 1024)), dim3(1024), 0,
+                               st, probes, P, nprobe, (int)nlist, rlo, rhi, cnt2, poff, pq, ps, ioff, ix->list_order,
+                               ix->list_off, qpi, vch, vs, dcap, desc);
+            return hipGetLastError();
+        }
         hipLaunchKernelGGL(item_desc_kernel, dim3((unsigned)((dcap + th - 1) / th)), dim3(th), 0, st, ioff,
                            ix->list_order, ix->list_off, poff, (int)nlist, qpi, vch, vs, dcap, desc);
-        if (reuse) {
-        } else if (lds_sort) {
-            hipLaunchKernelGGL(pair_place_kernel, dim3(kPairBlocks), dim3(1024), 0, st, probes, P, nprobe,
-                               (int)nlist, rlo, rhi, qmask, cnt2, poff, pq, ps, gate);
-        } else if (P > 0) {
+        if (!reuse && P > 0) {
             hipLaunchKernelGGL(pair_scatter_kernel, dim3(pblocks), dim3(th), 0, st, probes, P, nprobe, (int)nlist,
                                rlo, rhi, qmask, poff, fill, pq, ps);
         }
