@@ -63,17 +63,19 @@ __global__ __launch_bounds__(kSelThreads) void row_topk_kernel(
         if constexpr (R > 0) return kreg[u];
         else return f2key(d[j]);
     };
-    // Few of many (kk <= 128, kk non-empty chunks): a bound T from the threads'
-    // minima, a share of the kk from each wave in proportion to its chunks; at
-    // least kk keys lie at or under T, and usually not many more (kk 84 of 4096:
-    // about 130).  They are compacted in column order, and each finds its place
-    // by counting the smaller ones: two barriers and one pass over the keys
-    // instead of four passes and a sort (10,000 rows of 4096, kk 84: 109 us by
-    // the radix select below, which remains for longer rows, for more kk
-    // and for rows of which more than 256 keys pass).
+    // Few of many (kk <= 128, at most half the non-empty chunks): a bound T from
+    // the threads' minima, a share of the kk from each wave in proportion to its
+    // chunks; at least kk keys lie at or under T, and not many more (kk 84 of
+    // 4096: about 130).  They are compacted in column order, and each finds its
+    // place by counting the smaller ones: three barriers and one pass over the
+    // keys instead of four passes and a sort.  10,000 rows of 4096, kk 84: 109 ->
+    // 64 us; 1000 rows, kk 64: 19.5 -> 11.4.  With kk near the number of chunks T
+    // is their largest minimum and more than 256 keys pass, which falls back to
+    // the radix select at a loss (999 rows of 512, 128 chunks, kk 128: 12.9 ->
+    // 14.9), hence the half; longer rows and larger kk take it, too.
     if constexpr (R > 0) {
         const int chunks = (int)((N + R - 1) / R);
-        if (kk == k && kk > 0 && kk <= 128 && kk <= chunks) {
+        if (kk == k && kk > 0 && kk <= 128 && 2 * kk <= chunks) {
             const int lane = tid & 63, wid = tid >> 6;
             unsigned mn = 0xFFFFFFFFu;
 #pragma unroll
