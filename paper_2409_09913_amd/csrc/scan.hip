@@ -953,7 +953,8 @@ __global__ __launch_bounds__(kThreads, 2) void scan2_kernel(
 // just written, so from L2) into a wave-private LDS histogram; no block
 // barrier.  For kk <= 64 a shorter route usually applies: a bound from the
 // lanes' minima picks at most 64 candidates that contain the top-kk, and one
-// bitonic sort of (key, id) across the wave ranks them.
+// bitonic sort of (key, id) across the wave ranks them; for kk <= 128 a bound
+// from the lanes' two smallest keys leaves at most 256 for the key's search.
 //   mode 0: lowers the query's bound to it (the kk-th best candidate so far).
 //   mode 1: writes the exact top-kk ascending by (est, id): every candidate
 //           with a smaller key, and of those whose key equals the kk-th the
@@ -1136,16 +1137,16 @@ __global__ __launch_bounds__(256) void buf_select_kernel(int32_t* __restrict__ g
     // contain the top-kk; when they are at most 64, one sort across the wave
     // of (key, id) ranks them directly.  Otherwise the radix select below.
     bool fast = false;
-    if (kk <= 64 && c >= kk) {
-        // keys of batch `base` (the first from registers, the rest re-read
-        // from the buffer, just written, so from L2); past c all ones
-        auto batch = [&](int base, unsigned (&v)[kSelB]) {
+    // keys of batch `base` (the first from registers, the rest re-read
+    // from the buffer, just written, so from L2); past c all ones
+    auto batch = [&](int base, unsigned (&v)[kSelB]) {
 #pragma unroll
-            for (int k = 0; k < kSelB; ++k) {
-                const int t = base + lane + 64 * k;
-                v[k] = (base == 0) ? (t < c ? key0[k] : 0xFFFFFFFFu) : (t < c ? key_at(t) : 0xFFFFFFFFu);
-            }
-        };
+        for (int k = 0; k < kSelB; ++k) {
+            const int t = base + lane + 64 * k;
+            v[k] = (base == 0) ? (t < c ? key0[k] : 0xFFFFFFFFu) : (t < c ? key_at(t) : 0xFFFFFFFFu);
+        }
+    };
+    if (kk <= 64 && c >= kk) {
         unsigned mn = 0xFFFFFFFFu;
         for (int base = 0; base < c; base += 64 * kSelB) {
             unsigned v[kSelB];
@@ -1196,6 +1197,64 @@ __global__ __launch_bounds__(256) void buf_select_kernel(int32_t* __restrict__ g
                 }
                 return;
             }
+        }
+    }
+    // kk of 65 to 128: the same from the two smallest keys of every lane (the
+    // kk-th smallest of those 128 is at or above the kk-th smallest key), for up
+    // to 256 keys at or under it.  Both ranks are found bit by bit with ballots,
+    // in registers; the radix passes below go through LDS counters four times
+    // (a search of 999 queries, kk 100, three selects between rounds: 460 ->
+    // 452 us).
+    if (kk > 64 && kk <= 128 && c >= kk) {
+        unsigned m0 = 0xFFFFFFFFu, m1 = 0xFFFFFFFFu;
+        for (int base = 0; base < c; base += 64 * kSelB) {
+            unsigned v[kSelB];
+            batch(base, v);
+#pragma unroll
+            for (int k = 0; k < kSelB; ++k) { m1 = min(m1, max(m0, v[k])); m0 = min(m0, v[k]); }
+        }
+        unsigned T = 0;
+        for (int b = 31; b >= 0; --b) {
+            const unsigned x = T | (1u << b);
+            if (__popcll(__ballot(m0 < x)) + __popcll(__ballot(m1 < x)) < kk) T = x;
+        }
+        unsigned m = 0;
+        for (int base = 0; base < c; base += 64 * kSelB) {
+            unsigned v[kSelB];
+            batch(base, v);
+#pragma unroll
+            for (int k = 0; k < kSelB; ++k) m += (unsigned)__popcll(__ballot(base + lane + 64 * k < c && v[k] <= T));
+        }
+        if (m <= 256) {
+            const unsigned long long below = (1ull << lane) - 1ull;
+            unsigned run = 0;
+            for (int base = 0; base < c; base += 64 * kSelB) {
+                unsigned v[kSelB];
+                batch(base, v);
+#pragma unroll
+                for (int k = 0; k < kSelB; ++k) {
+                    const bool p = base + lane + 64 * k < c && v[k] <= T;
+                    const unsigned long long bal = __ballot(p);
+                    if (p) hist[w][run + (unsigned)__popcll(bal & below)] = v[k];
+                    run += (unsigned)__popcll(bal);
+                }
+            }
+            wave_lds_sync();
+            unsigned u[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) u[k] = lane + 64 * k < (int)m ? hist[w][lane + 64 * k] : 0xFFFFFFFFu;
+            wave_lds_sync();
+            auto under = [&](unsigned x) {
+                int n = 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) n += __popcll(__ballot(u[k] < x));
+                return n;
+            };
+            kth = 0;
+            for (int b = 31; b >= 0; --b)
+                if (under(kth | (1u << b)) < kk) kth |= 1u << b;
+            need_eq = (unsigned)(kk - under(kth));
+            fast = true;
         }
     }
     if (!fast && c >= kk) {

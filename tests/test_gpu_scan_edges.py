@@ -57,7 +57,7 @@ def test_pipeline_equals_small_batch(dp, bits, planes, metric):
 
 
 @pytest.mark.parametrize("nq,nprobe", [(1, 1), (1, 5), (2, 18), (17, 18), (40, 7)])
-@pytest.mark.parametrize("kk", [1, 20, 64, 65, 300])
+@pytest.mark.parametrize("kk", [1, 20, 64, 65, 128, 129, 300])
 def test_small_batch_slices(nq, nprobe, kk):
     """Slices that pass every key, a threshold's or their exact top-kk, against the pipeline."""
     print("slices", nq, nprobe, kk, flush=True)
