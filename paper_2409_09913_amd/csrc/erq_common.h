@@ -19,6 +19,10 @@ constexpr int kTileV = 32;      // vectors per packed code tile (rows of one 32x
 constexpr int kMaxDp = 4096;
 constexpr int kMaxDpNqt2 = 1536;  // largest dp whose two-tile query block fits the LDS
 constexpr int kMaxK = 1024;       // largest top-k / re-rank depth of a scan
+// Rows of one launch that gives every row a wave.  Row counts go up to 2^31 - 1,
+// and a launch of 2^32 threads or more runs only the remainder of the division
+// by 2^32, without an error (2^26 + 33 rows: 36 of them).
+constexpr int64_t kLaunchRows = (int64_t)1 << 24;
 
 // ---- status plumbing -------------------------------------------------------
 void set_error(const std::string& msg);

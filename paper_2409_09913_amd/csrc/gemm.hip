@@ -389,10 +389,16 @@ __global__ __launch_bounds__(256) void split_norm_kernel(const float* __restrict
 hipError_t launch_split_norm(const float* X, int64_t n, int K, unsigned short* planes, float* n2, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    if (n <= 2048 || !planes)
-        hipLaunchKernelGGL(split_norm_kernel<1>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, X, n, K, planes, n2);
-    else
-        hipLaunchKernelGGL(split_norm_kernel<4>, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, st, X, n, K, planes, n2);
+    for (int64_t r0 = 0; r0 < n; r0 += kLaunchRows) {
+        const int64_t m = std::min(kLaunchRows, n - r0);
+        const float* x = X + r0 * K;
+        unsigned short* pl = planes ? planes + 2 * r0 * K : nullptr;      // whole tiles: kLaunchRows is a multiple of 32
+        float* nn = n2 ? n2 + r0 : nullptr;
+        if (m <= 2048 || !planes)
+            hipLaunchKernelGGL(split_norm_kernel<1>, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, st, x, m, K, pl, nn);
+        else
+            hipLaunchKernelGGL(split_norm_kernel<4>, dim3((unsigned)((m + 15) / 16)), dim3(256), 0, st, x, m, K, pl, nn);
+    }
     return hipGetLastError();
 }
 

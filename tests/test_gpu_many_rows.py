@@ -1,0 +1,32 @@
+"""More rows than one launch can give a wave each (2^26 rows are 2^32 threads):
+17 GB of rows at 64 dimensions, far from the origin, so that the norms decide how
+the distances round and a row whose norm is missing gets another list.
+"""
+import pytest
+import torch
+
+from paper_2409_09913_amd import erq
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+DEV = torch.device("cuda:0")
+N, DP, C = (1 << 26) + 33, 64, 5
+
+
+@pytest.fixture(scope="module")
+def x():
+    if torch.cuda.mem_get_info()[0] < 64 << 30:
+        pytest.skip("needs 64 GB of device memory")
+    yield torch.randn((N, DP), device=DEV, generator=torch.Generator(device=DEV).manual_seed(1)).add_(1000.0)
+    torch.cuda.empty_cache()
+
+
+def test_kmeans(x):
+    cent, got = erq.kmeans(x, C, iters=1, seed=3)
+    for lo in (0, (1 << 24) - 500, (1 << 25) - 500, N - 1000):
+        want = erq.coarse_probe(x[lo:lo + 1000], cent, 1)[:, 0]
+        assert int((got[lo:lo + 1000] != want).sum()) == 0, lo
+    assert int(torch.bincount(got, minlength=C).sum()) == N
