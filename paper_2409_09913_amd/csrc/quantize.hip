@@ -44,6 +44,8 @@
 // use; the LDS (bins, magnitudes, levels: 8.2 KB at dp 768) lets 19 waves
 // share a CU.  32 bins per octave for one wave: 64 cost 15% at B = 4 (12 KB of
 // LDS and twice the bound tests) and gain nothing at B = 8.
+#include <algorithm>
+
 #include "erq_common.h"
 
 namespace erq {
@@ -658,8 +660,12 @@ static hipError_t launch_quantize_t(const float* rrot, int64_t n, int dp, int bi
 {
     const int cap = dp > 2 * kSortMax ? dp : 2 * kSortMax;
     const size_t sm = quant_smem(kBinsPerThread * NT, cap, dp);
-    hipLaunchKernelGGL(quantize_kernel<NT>, dim3((unsigned)n), dim3(NT), sm, st, rrot, n, dp, bits, cap, norm2,
-                       codes, f_add, f_rescale, cos_oo, fac);
+    constexpr int64_t rows = kLaunchRows * 64 / NT;
+    for (int64_t r = 0; r < n; r += rows)
+        hipLaunchKernelGGL(quantize_kernel<NT>, dim3((unsigned)std::min(rows, n - r)), dim3(NT), sm, st, rrot + r * dp,
+                           std::min(rows, n - r), dp, bits, cap, norm2 ? norm2 + r : nullptr, codes + r * dp,
+                           f_add ? f_add + r : nullptr, f_rescale ? f_rescale + r : nullptr,
+                           cos_oo ? cos_oo + r : nullptr, fac ? fac + r : nullptr);
     return hipGetLastError();
 }
 

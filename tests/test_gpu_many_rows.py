@@ -30,3 +30,10 @@ def test_kmeans(x):
         want = erq.coarse_probe(x[lo:lo + 1000], cent, 1)[:, 0]
         assert int((got[lo:lo + 1000] != want).sum()) == 0, lo
     assert int(torch.bincount(got, minlength=C).sum()) == N
+
+
+def test_quantize(x):
+    got = erq.quantize(x, 3)
+    for lo in (0, (1 << 24) - 500, (1 << 25) - 500, N - 1000):
+        for a, b in zip(got, erq.quantize(x[lo:lo + 1000].contiguous(), 3)):
+            assert int((a[lo:lo + 1000] != b).sum()) == 0, lo
