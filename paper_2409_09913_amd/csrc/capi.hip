@@ -931,7 +931,10 @@ int erq_index_build(erq_index ix, const float* x, int64_t n, const float* centro
         ERQ_HIP(hipMalloc(&ix->msb, std::max<int64_t>((int64_t)4 * dc * ix->ntiles, 256)));
         ERQ_HIP(hipMalloc(&ix->fac1, sizeof(float4) * std::max<int64_t>(n, 1)));
         if (n > 0) {
-            hipLaunchKernelGGL(msb_kernel, dim3(blocks(n * dc)), dim3(256), 0, st, codes_u, n * dc, ix->bits - 1, mu);
+            const int64_t step = kLaunchRows * 64;             // codes of a launch (one thread each)
+            for (int64_t i = 0; i < n * dc; i += step)
+                hipLaunchKernelGGL(msb_kernel, dim3(blocks(std::min(step, n * dc - i))), dim3(256), 0, st, codes_u + i,
+                                   std::min(step, n * dc - i), ix->bits - 1, mu + i);
             ERQ_HIP(hipGetLastError());
         }
         ERQ_HIP(launch_pack_n(mu, ix->list_off, ix->tile_off, C, dc, 1, ix->ntiles, ix->msb, st));

@@ -137,7 +137,11 @@ __global__ __launch_bounds__(256) void normalize_kernel(const float* __restrict_
 hipError_t launch_normalize(const float* x, int64_t n, int dp, float* out, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(normalize_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, x, n, dp, out);
+    for (int64_t r = 0; r < n; r += kLaunchRows) {
+        const int64_t m = n - r < kLaunchRows ? n - r : kLaunchRows;
+        hipLaunchKernelGGL(normalize_kernel, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, st, x + r * dp, m, dp,
+                           out + r * dp);
+    }
     return hipGetLastError();
 }
 

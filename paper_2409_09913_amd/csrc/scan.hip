@@ -1875,11 +1875,11 @@ __global__ __launch_bounds__(256) void pair_s2_kernel(const float* __restrict__ 
 __global__ __launch_bounds__(256) void scan_fac_kernel(const uint8_t* __restrict__ codes_u,
                                                        const int64_t* __restrict__ list_off, int nlist,
                                                        const float* __restrict__ cent_rot,
-                                                       const float2* __restrict__ fac, int64_t n, int dp, int ld,
-                                                       int bits, int ip, float2* __restrict__ sfac)
+                                                       const float2* __restrict__ fac, int64_t v0, int64_t n, int dp,
+                                                       int ld, int bits, int ip, float2* __restrict__ sfac)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t v = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t v = v0 + (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (v >= n) return;
     if (ip) {
         if (lane == 0) sfac[v] = make_float2(0.0f, 0.5f * fac[v].y);
@@ -1909,10 +1909,11 @@ __global__ __launch_bounds__(256) void scan1_fac_kernel(const uint8_t* __restric
                                                         const int64_t* __restrict__ list_off, int nlist,
                                                         const float* __restrict__ cent_rot, int ld,
                                                         const float2* __restrict__ fac, const float* __restrict__ l1,
-                                                        int64_t n, int dp, int bits, float4* __restrict__ fac1)
+                                                        int64_t v0, int64_t n, int dp, int bits,
+                                                        float4* __restrict__ fac1)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t v = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t v = v0 + (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (v >= n) return;
     int lo = 0, hi = nlist;
     while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (list_off[mid] <= v) lo = mid; else hi = mid; }
@@ -2470,8 +2471,9 @@ hipError_t launch_scan1_fac(const uint8_t* codes_u, const int64_t* list_off, int
                             hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(scan1_fac_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, codes_u, list_off,
-                       (int)nlist, cent_rot, ld, fac, l1, n, dp, bits, fac1);
+    for (int64_t v0 = 0; v0 < n; v0 += kLaunchRows)
+        hipLaunchKernelGGL(scan1_fac_kernel, dim3((unsigned)((std::min(kLaunchRows, n - v0) + 3) / 4)), dim3(256), 0, st,
+                           codes_u, list_off, (int)nlist, cent_rot, ld, fac, l1, v0, n, dp, bits, fac1);
     return hipGetLastError();
 }
 
@@ -2480,8 +2482,10 @@ hipError_t launch_scan_fac(const uint8_t* codes_u, const int64_t* list_off, int6
                            hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(scan_fac_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, codes_u, list_off,
-                       (int)nlist, cent_rot, fac, n, dp, ld, bits, metric != ERQ_METRIC_L2 ? 1 : 0, sfac);
+    for (int64_t v0 = 0; v0 < n; v0 += kLaunchRows)
+        hipLaunchKernelGGL(scan_fac_kernel, dim3((unsigned)((std::min(kLaunchRows, n - v0) + 3) / 4)), dim3(256), 0, st,
+                           codes_u, list_off, (int)nlist, cent_rot, fac, v0, n, dp, ld, bits,
+                           metric != ERQ_METRIC_L2 ? 1 : 0, sfac);
     return hipGetLastError();
 }
 

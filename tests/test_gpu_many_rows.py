@@ -37,3 +37,26 @@ def test_quantize(x):
     for lo in (0, (1 << 24) - 500, (1 << 25) - 500, N - 1000):
         for a, b in zip(got, erq.quantize(x[lo:lo + 1000].contiguous(), 3)):
             assert int((a[lo:lo + 1000] != b).sum()) == 0, lo
+
+
+def test_build_and_search(x):
+    """A two-stage index: its results on both scan paths are those of an index of the returned rows alone."""
+    y = x - 1000.0
+    q = torch.randn((64, DP), device=DEV, generator=torch.Generator(device=DEV).manual_seed(2))
+    P, cent = torch.eye(DP, device=DEV), y[::1 << 15].contiguous()
+    ix = erq.Index(DP, 2, cent.shape[0], P)
+    ix.set_two_stage(8.0)                             # no bound fails at 8
+    ix.build(y, cent)
+    ix.set_small_batch(0)
+    ids, est = ix.search(q, 8, 10)
+    ix.set_two_stage(0.0)
+    ix.set_small_batch(128)
+    ids1, est1 = ix.search(q, 8, 10)
+    ix.close()
+    assert int((ids != ids1).sum()) == 0 and int((est != est1).sum()) == 0
+    rows = ids.unique()
+    part = erq.Index(DP, 2, cent.shape[0], P)
+    part.build(y[rows].contiguous(), cent)
+    ids2, est2 = part.search(q, 8, 10)
+    part.close()
+    assert int((rows[ids2] != ids).sum()) == 0 and int((est2 != est).sum()) == 0
