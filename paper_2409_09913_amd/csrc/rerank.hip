@@ -108,12 +108,14 @@ hipError_t launch_rerank(const float* raw, int64_t n, int dp, const float* q, in
                          int64_t* out_ids, float* out_d, hipStream_t st, int metric)
 {
     if (nq <= 0) return hipSuccess;
-    if (metric != ERQ_METRIC_L2)
-        hipLaunchKernelGGL(rerank_kernel<true>, dim3((unsigned)nq), dim3(256), 0, st, raw, n, dp, q, cand, cand_est,
-                           kc, k, kc_q, k_q, out_ids, out_d);
-    else
-        hipLaunchKernelGGL(rerank_kernel<false>, dim3((unsigned)nq), dim3(256), 0, st, raw, n, dp, q, cand, cand_est,
-                           kc, k, kc_q, k_q, out_ids, out_d);
+    constexpr int64_t rows = kLaunchRows / 4;                  // of 256 threads
+    for (int64_t r = 0; r < nq; r += rows) {
+        const dim3 g((unsigned)(nq - r < rows ? nq - r : rows));
+        auto* kern = metric != ERQ_METRIC_L2 ? rerank_kernel<true> : rerank_kernel<false>;
+        hipLaunchKernelGGL(kern, g, dim3(256), 0, st, raw, n, dp, q + r * dp, cand + r * kc,
+                           cand_est ? cand_est + r * kc : nullptr, kc, k, kc_q ? kc_q + r : nullptr,
+                           k_q ? k_q + r : nullptr, out_ids + r * k, out_d + r * k);
+    }
     return hipGetLastError();
 }
 

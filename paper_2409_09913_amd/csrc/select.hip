@@ -6,6 +6,8 @@
 //    threads' minima and places by counting (few of many), else an exact radix
 //    select (4 passes of 8 bits), a stable compaction and a bitonic sort.
 //  * residuals r = x - c and ||r||^2 (FP64 accumulate) in list order.
+#include <algorithm>
+
 #include "erq_common.h"
 
 namespace erq {
@@ -284,12 +286,15 @@ hipError_t launch_row_topk(const float* D, int64_t n, int64_t N, int k, int32_t*
                            hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    const dim3 g((unsigned)n), b(kSelThreads);
-    if (N <= 4 * kSelThreads) hipLaunchKernelGGL(row_topk_kernel<4>, g, b, 0, st, D, N, k, idx, val);
-    else if (N <= 8 * kSelThreads) hipLaunchKernelGGL(row_topk_kernel<8>, g, b, 0, st, D, N, k, idx, val);
-    else if (N <= 16 * kSelThreads) hipLaunchKernelGGL(row_topk_kernel<16>, g, b, 0, st, D, N, k, idx, val);
-    else if (N <= 32 * kSelThreads) hipLaunchKernelGGL(row_topk_kernel<32>, g, b, 0, st, D, N, k, idx, val);
-    else hipLaunchKernelGGL(row_topk_kernel<0>, g, b, 0, st, D, N, k, idx, val);
+    constexpr int64_t rows = kLaunchRows * 64 / kSelThreads;
+    for (int64_t r = 0; r < n; r += rows, D += rows * N, idx += rows * k, val = val ? val + rows * k : nullptr) {
+        const dim3 g((unsigned)std::min(rows, n - r)), b(kSelThreads);
+        if (N <= 4 * kSelThreads) hipLaunchKernelGGL(row_topk_kernel<4>, g, b, 0, st, D, N, k, idx, val);
+        else if (N <= 8 * kSelThreads) hipLaunchKernelGGL(row_topk_kernel<8>, g, b, 0, st, D, N, k, idx, val);
+        else if (N <= 16 * kSelThreads) hipLaunchKernelGGL(row_topk_kernel<16>, g, b, 0, st, D, N, k, idx, val);
+        else if (N <= 32 * kSelThreads) hipLaunchKernelGGL(row_topk_kernel<32>, g, b, 0, st, D, N, k, idx, val);
+        else hipLaunchKernelGGL(row_topk_kernel<0>, g, b, 0, st, D, N, k, idx, val);
+    }
     return hipGetLastError();
 }
 

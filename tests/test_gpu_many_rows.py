@@ -60,3 +60,22 @@ def test_build_and_search(x):
     ids2, est2 = part.search(q, 8, 10)
     part.close()
     assert int((rows[ids2] != ids).sum()) == 0 and int((est2 != est).sum()) == 0
+
+
+def test_probe_and_rerank(x):
+    """2^24 queries and more: a workgroup of 256 threads each in the selection and the re-rank."""
+    nq = (1 << 24) + 5
+    q, cent = x[:nq], x[-3:].contiguous()
+    probes, pd = erq.coarse_probe(q, cent, 2, with_dist=True)
+    ix = erq.Index(DP, 1, 3, torch.eye(DP, device=DEV))
+    ix.build(cent, cent, keep_raw=True)
+    cand = torch.arange(nq, device=DEV).remainder(3)[:, None].repeat(1, 2)
+    cand[:, 1] = 2
+    ids, d = ix.rerank(q, cand, 1)
+    for lo in (0, (1 << 22) - 500, (1 << 23) - 500, nq - 1000):
+        at = slice(lo, lo + 1000)
+        p1, d1 = erq.coarse_probe(q[at].contiguous(), cent, 2, with_dist=True)
+        assert int((p1 != probes[at]).sum()) == 0 and int((d1 != pd[at]).sum()) == 0, lo
+        i1, d1 = ix.rerank(q[at].contiguous(), cand[at].contiguous(), 1)
+        assert int((i1 != ids[at]).sum()) == 0 and int((d1 != d[at]).sum()) == 0, lo
+    ix.close()
