@@ -734,8 +734,24 @@ hipError_t launch_probe_products(const unsigned short* A, int64_t n, int K, cons
 // the rounding in integer arithmetic; 256 x 128 tiles spill and take 1.2-1.7).
 // best (n slots, all ones) holds (key of the distance, column) when the columns
 // are split over gridDim.y > 1 workgroups; with one, they go straight to out.
+// The order is the probe selection's, that of the keys: a distance that is a NaN
+// comes first or last by its sign.  Where a norm says that there may be one (not
+// below kPlainNorm, so that |a.b| <= ||a|| ||b|| and the distance might overflow),
+// the wave compares keys from that tile on; else the floats, which is the same
+// (keys throughout would be 64 x 3 more instructions a tile).  Three workgroups
+// per CU is what the launch bound asks for: left to itself the compiler takes 198
+// registers for the second branch and two fit.
+constexpr float kPlainNorm = 1e37f;
+
+// order-preserving integer image of a float, and back
+__device__ inline unsigned order_key(float v) {
+    const unsigned u = __float_as_uint(v);
+    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+__device__ inline float key_value(unsigned k) { return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k); }
+
 template <int EPI>
-__global__ __launch_bounds__(256, 2) void assign_bf16x3_kernel(
+__global__ __launch_bounds__(256, 3) void assign_bf16x3_kernel(
     const float* __restrict__ A, int64_t n, int K, const unsigned short* __restrict__ B, int N,
     const float* __restrict__ an2, const float* __restrict__ bn2, int tiles_per_block,
     unsigned long long* __restrict__ best, int32_t* __restrict__ out)
@@ -743,6 +759,7 @@ __global__ __launch_bounds__(256, 2) void assign_bf16x3_kernel(
     constexpr int BK = 32;
     __shared__ __align__(16) unsigned short As[2][4][2][1024];           // buffer, row tile, chunk, hi | lo fragment
     __shared__ float s_bn[BN];
+    __shared__ int s_odd[BN / 64];                                       // some norm of the tile's columns is not plain
     __shared__ unsigned long long s_best[BM];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -760,9 +777,9 @@ __global__ __launch_bounds__(256, 2) void assign_bf16x3_kernel(
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
         const int64_t gr = row0 + 32 * (wm + a) + (lane & 31);
-        rn[a] = EPI == 1 && gr < n ? an2[gr] : 0.0f;
+        rn[a] = gr < n ? an2[gr] : 0.0f;
     }
-    // nothing below +inf (NaN is not): the lane's first column
+    bool odd = __any(!(rn[0] < kPlainNorm) || !(rn[1] < kPlainNorm));    // compare keys (the same in the whole wave)
     float bv[2] = {__builtin_huge_valf(), __builtin_huge_valf()};
     const int first = tile0 * BN + 32 * wn + out_row(lane, 0);
     int bc[2] = {first, first};
@@ -804,7 +821,12 @@ __global__ __launch_bounds__(256, 2) void assign_bf16x3_kernel(
         load_a(0);
         __syncthreads();                             // the last tile's reads of LDS are done
         store_a(0);
-        if (tid < BN) s_bn[tid] = EPI == 1 && tile * BN + tid < N ? bn2[tile * BN + tid] : 0.0f;
+        if (tid < BN) {
+            const float bn = tile * BN + tid < N ? bn2[tile * BN + tid] : 0.0f;
+            s_bn[tid] = bn;
+            const bool any = __any(!(bn < kPlainNorm));
+            if (lane == 0) s_odd[wid] = any ? 1 : 0;
+        }
         __syncthreads();
         int cur = 0;
         for (int k0 = 0; k0 < K; k0 += BK) {
@@ -842,29 +864,58 @@ __global__ __launch_bounds__(256, 2) void assign_bf16x3_kernel(
             cur ^= 1;
         }
         // columns ascend over tiles, b and r, so a strict comparison keeps the lowest
+        auto value = [&](int a, int b, int r, float bn) {
+            return EPI == 1 ? (rn[a] + bn) - 2.0f * acc[a][b][r] : -acc[a][b][r];
+        };
+        odd = odd || s_odd[0] != 0 || s_odd[1] != 0;
+        if (!odd) {
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+            for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int lc = 32 * (wn + b) + out_row(lane, r), gc = tile * BN + lc;
-                const float bn = s_bn[lc];
-                if (gc < N) {
+                for (int r = 0; r < 16; ++r) {
+                    const int lc = 32 * (wn + b) + out_row(lane, r), gc = tile * BN + lc;
+                    const float bn = s_bn[lc];
+                    if (gc < N) {
 #pragma unroll
-                    for (int a = 0; a < 2; ++a) {
-                        const float v = EPI == 1 ? (rn[a] + bn) - 2.0f * acc[a][b][r] : -acc[a][b][r];
-                        const bool better = v < bv[a];
-                        bv[a] = better ? v : bv[a];
-                        bc[a] = better ? gc : bc[a];
+                        for (int a = 0; a < 2; ++a) {
+                            const float v = value(a, b, r, bn);
+                            const bool better = v < bv[a];
+                            bv[a] = better ? v : bv[a];
+                            bc[a] = better ? gc : bc[a];
+                        }
                     }
                 }
-            }
+        } else {
+            unsigned bk[2];                          // nothing yet: above every key but that of the last NaN
+#pragma unroll
+            for (int a = 0; a < 2; ++a) bk[a] = tile == tile0 ? 0xFFFFFFFFu : order_key(bv[a]);
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int lc = 32 * (wn + b) + out_row(lane, r), gc = tile * BN + lc;
+                    const float bn = s_bn[lc];
+                    if (gc < N) {
+#pragma unroll
+                        for (int a = 0; a < 2; ++a) {
+                            // (of two NaNs in a sum either may come out: the row's)
+                            const float v = EPI == 1 && rn[a] != rn[a] ? rn[a] : value(a, b, r, bn);
+                            const unsigned k = order_key(v);
+                            const bool better = k < bk[a];
+                            bk[a] = better ? k : bk[a];
+                            bc[a] = better ? gc : bc[a];
+                        }
+                    }
+                }
+#pragma unroll
+            for (int a = 0; a < 2; ++a) bv[a] = key_value(bk[a]);
+        }
     }
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
-        const unsigned u = __float_as_uint(bv[a]);
-        const unsigned key = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
         if (bc[a] < N)
-            atomicMin(&s_best[32 * (wm + a) + (lane & 31)], ((unsigned long long)key << 32) | (unsigned)bc[a]);
+            atomicMin(&s_best[32 * (wm + a) + (lane & 31)],
+                      ((unsigned long long)order_key(bv[a]) << 32) | (unsigned)bc[a]);
     }
     __syncthreads();
     if (tid < BM && row0 + tid < n) {

@@ -64,3 +64,47 @@ def test_means_of_long_lists(n, dp, C):
         m = x[a0 == l].double()
         want = (m.mean(0) if len(m) else c0[l].double()).float()
         assert torch.allclose(c1[l], want, rtol=2 ** -23, atol=1e-12 + 2.0 ** -50 * float(m.abs().sum(0).max()) / max(len(m), 1))
+
+
+def plant(kind, x, c):
+    """Rows and centroids whose distances overflow or are not numbers, some of them or all."""
+    inf, nan = float("inf"), float("nan")
+    n, C = len(x), len(c)
+    if kind == "all overflow":
+        x *= 1e19
+        c *= 1e19
+    elif kind == "last centroids overflow":
+        x *= 1e19
+        c[C - 3:] *= 1e19
+    elif kind == "first centroids overflow":
+        x *= 1e19
+        c[:3] *= 1e19
+    elif kind == "some rows overflow":
+        x[n // 2:] *= 1e19
+        c *= 1e19
+    elif kind == "nan":
+        x[n // 3, 5] = nan
+        c[C // 2, 7] = -nan
+        c[C - 1, 3] = nan
+    elif kind == "inf":
+        x[n // 3, 5], x[n // 2, 9] = inf, -inf
+        c[0, 5], c[C // 2, 7] = inf, -inf
+
+
+@pytest.mark.parametrize("kind", ["all overflow", "last centroids overflow", "first centroids overflow",
+                                  "some rows overflow", "nan", "inf"])
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+@pytest.mark.parametrize("n,dp,C", [(300, 64, 100), (5000, 128, 700), (40_000, 64, 300)])
+def test_lists_of_distances_that_are_not_numbers(n, dp, C, metric, kind):
+    """The order is the probe's there, too."""
+    print("assign", n, dp, C, metric, kind, flush=True)
+    x, cent = rows(n, dp, 1), rows(C, dp, 2)
+    plant(kind, x, cent)
+    ix = erq.Index(dp, 4, C, torch.eye(dp, device=DEV), metric=metric)
+    ix.build(x, cent)
+    off, ids = ix.export()[:2]
+    ix.close()
+    got = torch.empty(n, dtype=torch.int64, device=DEV)
+    got[ids] = torch.repeat_interleave(torch.arange(C, device=DEV), off.diff())
+    want = erq.coarse_probe(x, cent, 1, metric=metric)[:, 0]
+    assert int((got != want).sum()) == 0
