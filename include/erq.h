@@ -173,7 +173,9 @@ int erq_index_set_two_stage(erq_index idx, float eps0);
    products <y_u, q_int> and <y_u, q_lo> both exact in int32 on the matrix
    cores, the error 254 times smaller, at twice the matrix-core work per
    query (32 queries per work item instead of 64).  planes = 2 needs
-   bits >= 5 and no two-stage scan (ERQ_EUNSUPPORTED).  A query-time setting:
+   bits >= 5 and no two-stage scan (ERQ_EUNSUPPORTED).  Above 2048 code
+   dimensions a work item's two planes do not fit the LDS: batches of every
+   size take the small-batch path there.  A query-time setting:
    the codes do not change; saved with the index. */
 int erq_index_set_query_planes(erq_index idx, int32_t planes);
 

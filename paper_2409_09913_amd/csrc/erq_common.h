@@ -18,6 +18,7 @@ constexpr int kWave = 64;
 constexpr int kTileV = 32;      // vectors per packed code tile (rows of one 32x32 MFMA tile)
 constexpr int kMaxDp = 4096;
 constexpr int kMaxDpNqt2 = 1536;  // largest dp whose two-tile query block fits the LDS
+constexpr int kMaxDpPlanes2 = 2048;  // largest dp whose block of 32 queries in two planes fits the LDS (64 dp + 31.5 KB)
 constexpr int kMaxK = 1024;       // largest top-k / re-rank depth of a scan
 // Rows of one launch that gives every row a wave.  Row counts go up to 2^31 - 1,
 // and a launch of 2^32 threads or more runs only the remainder of the division

@@ -62,6 +62,25 @@ def test_two_plane_scan_parity(B, dp, kk):
     ix.close()
 
 
+@pytest.mark.parametrize("B,dp,nq,kk", [(5, 2048, 150, 10), (5, 2112, 129, 10), (8, 2112, 600, 5), (6, 3072, 150, 300)])
+def test_two_plane_large_batches_of_wide_rows(B, dp, nq, kk):
+    """Above the small-batch threshold, at the largest width of the pair-grouped pipeline and past it."""
+    say("two-plane batch B", B, "dp", dp, "queries", nq, "kk", kk)
+    nl, nprobe = 20, 17
+    ix, (off, ids, codes, fa, fr, crot) = _imported(3000, nl, dp, B, seed=800 + B + dp)
+    qrot = synth.random_rotated(nq, dp, seed=801 + B)
+    probes = synth.random_probes(nq, nl, nprobe, seed=802 + B)
+    gi, ge = [t.cpu().numpy() for t in ix.scan(dev(qrot), dev(probes), kk)]
+    for lo in range(0, nq, 100):                          # the small-batch path where kk <= 256
+        at = slice(lo, lo + 100)
+        si, se = [t.cpu().numpy() for t in ix.scan(dev(qrot[at]), dev(probes[at]), kk)]
+        assert np.array_equal(si, gi[at]) and np.array_equal(se, ge[at])
+    m = 40
+    oi, oe = oracle.search(off, ids, codes, fa, fr, crot, qrot[:m], probes[:m], B, kk, est_mode=3)
+    compare_topk(gi[:m], ge[:m], oi, oe, CandTerms(off, ids, codes, fa, fr, crot, qrot[:m], probes[:m], B))
+    ix.close()
+
+
 @pytest.mark.parametrize("kk", [16, 100])
 def test_two_plane_exact_fallback_ties(kk):
     """All members of a list tie exactly; lists of 9000 and 5000 members keep
