@@ -273,7 +273,7 @@ def main():
     dt = time.perf_counter() - ts
     scan_ms, scan_n = erq.profile_read("scan")
     tot, raw = {}, {}
-    for kname in ("rotate", "probe", "scan", "scan_a", "scan_b", "scan_c", "rerank"):
+    for kname in ("probe", "scan", "scan_a", "scan_b", "scan_c", "rerank"):   # probe: its launch rotates the queries, too
         ms, nl = erq.profile_read(kname)
         tot[kname] = ms / max(nl, 1)
         raw[kname] = (ms, nl)

@@ -399,7 +399,10 @@ int erq_index_tune(erq_index idx, const float* q, int64_t nq, int32_t nprobe, in
 /* recorded on the stream it is launched on.  Names: "scan" (the int8 matrix- */
 /* core scan, all passes), "scan_a" (its first bound), "scan_b" (each launch */
 /* of the bounded scan), "scan_c" (final selection and exact fallback),     */
-/* "quantize", "rotate", "probe", "rerank".  "scan_redo_pairs"              */
+/* "quantize", "rotate" (rotations launched by themselves: erq_rotate and    */
+/* the build's), "probe" (the coarse probe and its selection; in erq_search  */
+/* the rotation of the queries too, whose product is part of that launch; in */
+/* the build the assignment to lists), "rerank".  "scan_redo_pairs"          */
 /* returns in total_ms the number of pairs re-scanned by the exact fallback,*/
 /* "scan2_groups" the groups of 64 members whose full codes the two-stage   */
 /* scan did not read (total_ms) and all its groups (launches); both are     */

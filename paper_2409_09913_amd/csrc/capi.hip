@@ -260,13 +260,9 @@ int probe_impl(const float* q, int64_t nq, float* qn, const unsigned short* cent
 {
     unsigned short* qp = (unsigned short*)ws;
     float* D = (float*)((char*)ws + align256(sizeof(unsigned short) * plane_elems(nq, dp)));
-    int pr = prof_begin(PK_ROTATE, st);
     ERQ_HIP(launch_split_norm(q, nq, dp, qp, qn, st));
-    prof_end(pr, st);
-    pr = prof_begin(PK_PROBE, st);
     ERQ_HIP(launch_probe_products(qp, nq, dp, qn, cent_pl, nlist, cent_n2, metric != ERQ_METRIC_L2, D, R, dc, rot, st));
     ERQ_HIP(launch_row_topk(D, nq, nlist, nprobe, probes, pdist, st));
-    prof_end(pr, st);
     return ERQ_OK;
 }
 
@@ -480,9 +476,13 @@ int erq_coarse_probe(const float* q, int64_t nq, const float* centroids, int64_t
     float* qn = (float*)w; w += align256(sizeof(float) * nq);
     float* cn = (float*)w; w += align256(sizeof(float) * nlist);
     unsigned short* cp = (unsigned short*)w; w += align256(sizeof(unsigned short) * plane_elems(nlist, dp));
-    ERQ_HIP(launch_split_norm(centroids, nlist, dp, cp, cn, (hipStream_t)stream));
-    return probe_impl(q, nq, qn, cp, cn, nlist, dp, nprobe, probes, pdist, nullptr, 0, nullptr, w, (hipStream_t)stream,
-                      metric);
+    hipStream_t st = (hipStream_t)stream;
+    const int pr = prof_begin(PK_PROBE, st);
+    ERQ_HIP(launch_split_norm(centroids, nlist, dp, cp, cn, st));
+    if (int rc = probe_impl(q, nq, qn, cp, cn, nlist, dp, nprobe, probes, pdist, nullptr, 0, nullptr, w, st, metric))
+        return rc;
+    prof_end(pr, st);
+    return ERQ_OK;
 }
 
 int erq_sample_rotation(int32_t dp, uint64_t seed, float* P_host)
@@ -1098,9 +1098,11 @@ static int search_run(Index* ix, const float* q, int64_t nq, int nprobe, int k, 
     // query planes.  The probe's ||q - c||^2 = ||q' - c'||^2 (P orthogonal) is the
     // scan's ||s||^2 (L2), its -<q, c> = -<q', c'> the scan's per-pair term
     // (inner-product metrics).
+    const int pr = prof_begin(PK_PROBE, st);
     if (int rc = probe_impl(q, nq, qn, ix->cent_pl, ix->cent_n2, ix->nlist, ix->dp, nprobe, probes, pdist, ix->pt_pl,
                             ix->dc, qrot, w, st, ix->metric))
         return rc;
+    prof_end(pr, st);
     const bool per_query = nprobe_q || k_q || rerank_q;
     if (per_query) {
         hipLaunchKernelGGL(query_params_kernel, dim3(blocks(nq)), dim3(256), 0, st, nq, nprobe, k, rerank_k, nprobe_q,

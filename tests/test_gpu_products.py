@@ -68,3 +68,23 @@ def test_fp32_rotation_does_not_depend_on_the_batch(dp):
     for n in (1, 15, 17, 33, 500, 1400, 3001):
         got = erq.rotate(x[:n].contiguous(), P).view(torch.int32)
         assert torch.equal(got, want[:n]), n
+
+
+def test_timer_names():
+    """"rotate" counts rotations launched by themselves; a search's is part of the probe's launch."""
+    g = torch.Generator(device=DEV).manual_seed(5)
+    x = torch.randn((500, 128), device=DEV, generator=g)
+    P = torch.linalg.qr(torch.randn((128, 128), device=DEV, generator=g))[0].contiguous()
+    ix = erq.Index(128, 4, 8, P)
+    calls = [(lambda: erq.rotate(x, P, precision=2), 1, 0), (lambda: erq.coarse_probe(x, x[:8].contiguous(), 3), 0, 1),
+             (lambda: ix.build(x, x[:8].contiguous()), 1, 1), (lambda: ix.search(x, 4, 5), 0, 1)]
+    erq.profile_enable(True)
+    erq.profile_read("rotate", reset=True)
+    try:
+        for call, rotate, probe in calls:
+            call()
+            assert (erq.profile_read("rotate")[1], erq.profile_read("probe")[1]) == (rotate, probe)
+            erq.profile_read("rotate", reset=True)
+    finally:
+        erq.profile_enable(False)
+    ix.close()
