@@ -576,14 +576,15 @@ hipError_t launch_mm_t(const unsigned short* A, int64_t n, int K, const float* a
     return hipGetLastError();
 }
 
-// The same products for many rows: 4 waves take 256 x 128 outputs, 4 x 2 tiles
-// each, with both operands in LDS (two buffers of one K chunk, 24 KB each, so
-// two workgroups share a CU and fill each other's waits).  The fragments are
-// copied global -> LDS without registers; a wave has read a stage's fragments
-// before it issues the next stage's copies, so the compiler's wait for copies in
-// front of LDS reads never meets one in flight.  One barrier per chunk.
-constexpr int kBigR = 8, kBigC = 4;                   // row and column tiles of 32 per workgroup
-constexpr int kBigStage = (kBigR + kBigC) * 2048;     // bytes of a stage: hi and lo fragment per tile
+// The same products with both operands in LDS, in two buffers of KC K chunks: 4
+// waves take 32 BR x 128 outputs, BR / 2 x 2 tiles each.  BR = 8, KC = 1, for
+// many rows (24 KB a buffer, so two workgroups share a CU and fill each other's
+// waits); BR = 4, KC = 2 where 256 rows would be mostly padding or leave CUs
+// idle.  The fragments are copied global -> LDS without registers; a wave has
+// read a buffer's fragments before it issues the next copies, so the compiler's
+// wait for copies in front of LDS reads never meets one in flight.  One barrier
+// per buffer.
+constexpr int kBigC = 4;                              // column tiles of 32 per workgroup
 
 typedef const __attribute__((address_space(1))) void* gptr;
 typedef __attribute__((address_space(3))) void* lptr;
@@ -594,107 +595,133 @@ __device__ inline void copy_chunk(const uint4* g, char* l) {
     __builtin_amdgcn_global_load_lds((gptr)(g + 64), (lptr)(l + 1024), 16, 0, 0);
 }
 
+template <int BR, int KC>
 __global__ __launch_bounds__(256, 2) void mm_big_kernel(const unsigned short* __restrict__ A, int64_t n, int K,
                                                         const float* __restrict__ an2, MmOut o0, MmOut o1, int cb0,
                                                         int64_t rb, int64_t nblk)
 {
-    __shared__ __align__(16) char smem[2][kBigStage];
+    constexpr int kChunk = (BR + kBigC) * 2048;       // bytes of a chunk: hi and lo fragment per tile
+    constexpr int RW = BR / 2, RC = BR / 4;           // row tiles a wave multiplies and copies
+    __shared__ __align__(16) char smem[2][KC * kChunk];
     const int lane = threadIdx.x & 63;
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t per = (nblk + 7) >> 3, blk = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     if ((int64_t)(blockIdx.x >> 3) >= per || blk >= nblk) return;
     int cb = (int)(blk / rb);
-    const int64_t rt0 = (blk - cb * rb) * kBigR;
+    const int64_t rt0 = (blk - cb * rb) * BR;
     const bool second = cb >= cb0;
     const MmOut& o = second ? o1 : o0;
     if (second) cb -= cb0;
     const int ct0 = cb * kBigC;
     const int64_t rtn = (n + 31) >> 5;
     const int ctn = (o.N + 31) >> 5;
-    const int S = K >> 4;
-    // wave w copies row tiles 2w and 2w + 1 and column tile w
-    const uint4* ga[2];
+    const int S = K >> 4;                                                // chunks: a multiple of 4
+    // wave w copies row tiles RC w .. and column tile w
+    const uint4* ga[RC];
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-        ga[u] = (const uint4*)A + (rt0 + 2 * wid + u < rtn ? rt0 + 2 * wid + u : rtn - 1) * S * 128 + lane;
+    for (int u = 0; u < RC; ++u)
+        ga[u] = (const uint4*)A + (rt0 + RC * wid + u < rtn ? rt0 + RC * wid + u : rtn - 1) * S * 128 + lane;
     const uint4* gb = (const uint4*)o.B + (int64_t)(ct0 + wid < ctn ? ct0 + wid : ctn - 1) * S * 128 + lane;
-    auto copy = [&](int s) {
-        char* l = smem[s & 1];
-        copy_chunk(ga[0] + s * 128, l + (2 * wid) * 2048);
-        copy_chunk(ga[1] + s * 128, l + (2 * wid + 1) * 2048);
-        copy_chunk(gb + s * 128, l + (kBigR + wid) * 2048);
-    };
-    const int wr = (wid >> 1) * 4, wc = (wid & 1) * 2;
-    v16f acc[4][2];
+    auto copy = [&](int s, int buf) {
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+        for (int c = 0; c < KC; ++c) {
+            char* l = smem[buf] + c * kChunk;
+#pragma unroll
+            for (int u = 0; u < RC; ++u) copy_chunk(ga[u] + (s + c) * 128, l + (RC * wid + u) * 2048);
+            copy_chunk(gb + (s + c) * 128, l + (BR + wid) * 2048);
+        }
+    };
+    const int wr = (wid >> 1) * RW, wc = (wid & 1) * 2;
+    v16f acc[RW][2];
+#pragma unroll
+    for (int a = 0; a < RW; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
-    copy(0);
-    for (int s = 0; s < S; ++s) {
-        const char* cur = smem[s & 1] + lane * 16;
-        __syncthreads();                              // this chunk is in LDS; the other buffer's readers are done
-        auto frag = [&](int tile, int plane) {
-            v8bf v;
-            __builtin_memcpy(&v, cur + tile * 2048 + plane * 1024, 16);
-            return v;
-        };
-        v8bf ah[4], al[4], bh[2], bl[2];
+    copy(0, 0);
+    int buf = 0;
+    for (int s = 0; s < S; s += KC, buf ^= 1) {
+        const char* cur = smem[buf] + lane * 16;
+        __syncthreads();                              // these chunks are in LDS; the other buffer's readers are done
+        v8bf ah[KC][RW], al[KC][RW], bh[KC][2], bl[KC][2];
 #pragma unroll
-        for (int b = 0; b < 2; ++b) { bh[b] = frag(kBigR + wc + b, 0); bl[b] = frag(kBigR + wc + b, 1); }
+        for (int c = 0; c < KC; ++c) {
+            auto frag = [&](int tile, int plane) {
+                v8bf v;
+                __builtin_memcpy(&v, cur + c * kChunk + tile * 2048 + plane * 1024, 16);
+                return v;
+            };
 #pragma unroll
-        for (int a = 0; a < 4; ++a) { ah[a] = frag(wr + a, 0); al[a] = frag(wr + a, 1); }
+            for (int b = 0; b < 2; ++b) { bh[c][b] = frag(BR + wc + b, 0); bl[c][b] = frag(BR + wc + b, 1); }
+#pragma unroll
+            for (int a = 0; a < RW; ++a) { ah[c][a] = frag(wr + a, 0); al[c][a] = frag(wr + a, 1); }
+        }
         __builtin_amdgcn_sched_barrier(0);
-        if (s + 1 < S) copy(s + 1);
+        if (s + KC < S) copy(s + KC, buf ^ 1);
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+        for (int c = 0; c < KC; ++c) {
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[a], bh[b], acc[a][b], 0, 0, 0);
+            for (int a = 0; a < RW; ++a)
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+                for (int b = 0; b < 2; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[c][a], bh[c][b], acc[a][b], 0, 0, 0);
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bl[b], acc[a][b], 0, 0, 0);
+            for (int a = 0; a < RW; ++a)
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+                for (int b = 0; b < 2; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[c][a], bl[c][b], acc[a][b], 0, 0, 0);
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bh[b], acc[a][b], 0, 0, 0);
+            for (int a = 0; a < RW; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[c][a], bh[c][b], acc[a][b], 0, 0, 0);
+        }
     }
 #pragma unroll
-    for (int a = 0; a < 4; ++a) store_tile<2>(acc[a], o, an2, n, rt0 + wr + a, ct0 + wc, lane);
+    for (int a = 0; a < RW; ++a) store_tile<2>(acc[a], o, an2, n, rt0 + wr + a, ct0 + wc, lane);
 }
 
+template <int BR, int KC>
 hipError_t launch_mm_big(const unsigned short* A, int64_t n, int K, const float* an2, const MmOut& o0, const MmOut& o1,
                          hipStream_t st)
 {
-    const int64_t rb = (n + 32 * kBigR - 1) / (32 * kBigR);
+    const int64_t rb = (n + 32 * BR - 1) / (32 * BR);
     const int cb0 = (o0.N + 32 * kBigC - 1) / (32 * kBigC), cb1 = (o1.N + 32 * kBigC - 1) / (32 * kBigC);
     const int64_t nblk = rb * (cb0 + cb1);
-    hipLaunchKernelGGL(mm_big_kernel, dim3((unsigned)((nblk + 7) / 8 * 8)), dim3(256), 0, st, A, n, K, an2, o0, o1, cb0,
-                       rb, nblk);
+    hipLaunchKernelGGL((mm_big_kernel<BR, KC>), dim3((unsigned)((nblk + 7) / 8 * 8)), dim3(256), 0, st, A, n, K, an2,
+                       o0, o1, cb0, rb, nblk);
     return hipGetLastError();
 }
 
-// The 256 x 128 tiles where they give every CU one (10,000 x 4,864 x 768: 199
-// us against 257 with 2 x 2 tiles per wave and no LDS, 270 with 128 x 128 tiles
-// staged through registers; 2,000 rows: 56 against 61).  Else every wave loads
-// its own fragments: 2 x 2 tiles where that leaves two waves for every SIMD,
-// 2 x 1 down to one (1000 x 5056 x 960: 46 us against 62), below that 1 x 1
-// with the loads 8 chunks ahead, as the chain of one wave is what counts (1 x
-// 1,792 x 768: 10 us against 51 with 128 x 128 tiles; 500 x 4,096 x 3072: 60
-// against 240).
+// 256 x 128 tiles where they give every CU one (10,000 x 4,864 x 768: 199 us
+// against 257 with 2 x 2 tiles per wave and no LDS, 270 with 128 x 128 tiles
+// staged through registers; 2,000 rows: 56 against 61), unless a quarter of their
+// rows or more would be padding: 128 x 128 tiles for 65 to 128 rows and for 257 to
+// 384 (100 x 40,000 x 1536: 67 us against 105, 300 x 20,000 x 1536: 74 against 105),
+// and up to 64 rows the waves' own loads (1 x 40,000 x 768: 24 us against 57).
+// Else every wave loads its own fragments: 2 x 2 tiles where that leaves two
+// waves for every SIMD, 2 x 1 down to one (1000 x 5056 x 960: 46 us against 62),
+// below that 1 x 1 with the loads 8 chunks ahead, as the chain of one wave is what
+// counts (1 x 1,792 x 768: 10 us against 51 with 128 x 128 tiles; 500 x 4,096 x
+// 3072: 60 against 240).  Instead of 2 x 1, 128 x 128 tiles where there is one for
+// every CU and K is long: each wave's reading of its fragments from L2 then costs
+// more than the barriers (200 x 16,384 x 4096: 125 us against 221, x 1536: 42
+// against 64).
 hipError_t launch_mm(const unsigned short* A, int64_t n, int K, const float* an2, const MmOut& o0, const MmOut& o1,
                      hipStream_t st)
 {
     const int64_t waves = (n + 63) / 64 * ((o0.N + 63) / 64 + (o1.N + 63) / 64);
-    if ((n + 255) / 256 * ((o0.N + 127) / 128 + (o1.N + 127) / 128) >= 256)
-        return launch_mm_big(A, n, K, an2, o0, o1, st);
+    const int64_t cols = (o0.N + 127) / 128 + (o1.N + 127) / 128, rows = (n + 127) / 128;
+    if ((rows + 1) / 2 * cols >= 256) {
+        if (n <= 32) return launch_mm_t<1, 1, 1, 8>(A, n, K, an2, o0, o1, st);
+        if (n <= 64) return launch_mm_t<1, 1, 2, 8>(A, n, K, an2, o0, o1, st);
+        if (rows == 1 || rows == 3) return launch_mm_big<4, 2>(A, n, K, an2, o0, o1, st);
+        return launch_mm_big<8, 1>(A, n, K, an2, o0, o1, st);
+    }
     if (waves >= 2048) return launch_mm_t<2, 2, 2, 2>(A, n, K, an2, o0, o1, st);
     if (n <= 32) return launch_mm_t<1, 1, 1, 8>(A, n, K, an2, o0, o1, st);
+    if (waves >= 900 && K >= (waves >= 1024 ? 1536 : 3072) && rows * cols >= 256) return launch_mm_big<4, 2>(A, n, K, an2, o0, o1, st);
     if (waves >= 1024) return launch_mm_t<2, 1, 2, 2>(A, n, K, an2, o0, o1, st);
     return launch_mm_t<1, 1, 2, 8>(A, n, K, an2, o0, o1, st);
 }

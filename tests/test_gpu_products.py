@@ -70,6 +70,21 @@ def test_fp32_rotation_does_not_depend_on_the_batch(dp):
         assert torch.equal(got, want[:n]), n
 
 
+@pytest.mark.parametrize("n,nl,dp", [(32, 32_769, 64), (64, 32_800, 64), (65, 32_769, 64), (128, 33_000, 192),
+                                     (257, 16_500, 64), (300, 20_000, 128), (384, 16_400, 64), (200, 16_384, 1536),
+                                     (255, 16_390, 1600), (900, 4_400, 1536)])
+def test_probe_does_not_depend_on_the_batch(n, nl, dp):
+    """Few queries over many lists (128 x 128 tiles among others) against the same queries 16 at a time."""
+    print("probe products", n, nl, dp, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(n + nl)
+    q = torch.randn((n, dp), device=DEV, generator=g)
+    c = torch.randn((nl, dp), device=DEV, generator=g)
+    probes, d = erq.coarse_probe(q, c, 100, with_dist=True)
+    for lo in range(0, n, 16):
+        p1, d1 = erq.coarse_probe(q[lo:lo + 16].contiguous(), c, 100, with_dist=True)
+        assert torch.equal(p1, probes[lo:lo + 16]) and torch.equal(d1, d[lo:lo + 16]), lo
+
+
 def test_timer_names():
     """"rotate" counts rotations launched by themselves; a search's is part of the probe's launch."""
     g = torch.Generator(device=DEV).manual_seed(5)
