@@ -15,9 +15,9 @@ namespace erq {
 // launchers defined in the other translation units
 size_t plane_elems(int64_t n, int K);
 hipError_t launch_split_norm(const float* X, int64_t n, int K, unsigned short* planes, float* n2, hipStream_t st);
-hipError_t launch_split_t(const float* x, int K, int N, unsigned short* planes, hipStream_t st);
-hipError_t launch_gemm_bf16x3(const unsigned short* A, int64_t n, const unsigned short* B, int64_t N, int K,
-                              float* out, int64_t ldo, hipStream_t st);
+hipError_t launch_split_t(const float* x, int K, int ld, int N, unsigned short* planes, hipStream_t st);
+hipError_t launch_gemm_bf16x3(const unsigned short* A, int64_t n, const unsigned short* B0, int N0,
+                              const unsigned short* B1, int N1, int K, float* out, int64_t ldo, hipStream_t st);
 hipError_t launch_probe_products(const unsigned short* A, int64_t n, int K, const float* an2, const unsigned short* B,
                                  int64_t N, const float* bn2, int neg_ip, float* D, const unsigned short* R, int NR,
                                  float* rot, hipStream_t st);
@@ -273,6 +273,12 @@ size_t probe_ws(int64_t nq, int64_t nlist, int dp) {
            align256(sizeof(unsigned short) * plane_elems(nlist, dp));
 }
 
+// Scratch of a call that is worth cutting in two: an allocation under 2 MiB and
+// its release come from the runtime's cache (2 us together), one from there on
+// goes to the driver (25 us).
+constexpr size_t kCachedAlloc = ((size_t)2 << 20) - 1;
+bool cut_alloc(size_t bytes) { return bytes > kCachedAlloc && bytes <= 2 * kCachedAlloc; }
+
 // One device allocation cut into 256-byte aligned pieces: a first walk with no
 // base adds the sizes up, the second one hands the pieces out.  Allocations of
 // a build or a k-means are few and small: device memory given back and taken
@@ -422,14 +428,24 @@ int erq_rotate(const float* x, int64_t n, int32_t dp, const float* P, int32_t pr
     if (precision == 2) {
         // the search's rotation: BF16 planes of x and of P^T, three products per K chunk
         if (n == 0) return ERQ_OK;
-        struct Tmp { void* p[2] = {nullptr, nullptr}; ~Tmp() { for (void* q : p) hipFree(q); } } t;
-        ERQ_HIP(hipMalloc(&t.p[0], sizeof(unsigned short) * plane_elems(n, dp)));
-        ERQ_HIP(hipMalloc(&t.p[1], sizeof(unsigned short) * plane_elems(dp, dp)));
-        auto* xp = (unsigned short*)t.p[0]; auto* pp = (unsigned short*)t.p[1];
+        // P^T in one piece or two, the rows in one turn or a few through one buffer
+        // (1000 x 768: 55 us, 95 with one allocation of 2.4 MB and one of 3.1)
+        struct Tmp { void* p[3] = {nullptr, nullptr, nullptr}; ~Tmp() { for (void* q : p) hipFree(q); } } t;
+        const int d0 = cut_alloc(sizeof(unsigned short) * plane_elems(dp, dp)) ? dp / 2 : dp, d1 = dp - d0;
+        const int64_t m = cut_alloc(sizeof(unsigned short) * plane_elems(n, dp))
+                              ? (int64_t)(kCachedAlloc / (32 * 4 * (size_t)dp)) * 32 : n;
+        ERQ_HIP(hipMalloc(&t.p[0], sizeof(unsigned short) * plane_elems(m, dp)));
+        ERQ_HIP(hipMalloc(&t.p[1], sizeof(unsigned short) * plane_elems(d0, dp)));
+        if (d1 > 0) ERQ_HIP(hipMalloc(&t.p[2], sizeof(unsigned short) * plane_elems(d1, dp)));
+        auto* xp = (unsigned short*)t.p[0]; auto* p0 = (unsigned short*)t.p[1]; auto* p1 = (unsigned short*)t.p[2];
         int pr = prof_begin(PK_ROTATE, st);
-        ERQ_HIP(launch_split_norm(x, n, dp, xp, nullptr, st));
-        ERQ_HIP(launch_split_t(P, dp, dp, pp, st));
-        ERQ_HIP(launch_gemm_bf16x3(xp, n, pp, dp, dp, out, dp, st));
+        ERQ_HIP(launch_split_t(P, dp, dp, d0, p0, st));
+        if (d1 > 0) ERQ_HIP(launch_split_t(P + d0, dp, dp, d1, p1, st));
+        for (int64_t r = 0; r < n; r += m) {
+            const int64_t c = std::min(m, n - r);
+            ERQ_HIP(launch_split_norm(x + r * dp, c, dp, xp, nullptr, st));
+            ERQ_HIP(launch_gemm_bf16x3(xp, c, p0, d0, p1, d1, dp, out + r * dp, dp, st));
+        }
         prof_end(pr, st);
         ERQ_HIP(hipStreamSynchronize(st));          // before the scratch planes are freed
         return ERQ_OK;
@@ -520,7 +536,7 @@ int erq_index_create(int32_t dp, int32_t bits, int64_t nlist, const float* P, ui
                      : hipMemcpyAsync(ix->P, hP.data(), sizeof(float) * dp * dp, hipMemcpyHostToDevice,
                                       (hipStream_t)stream);
     if (e == hipSuccess) e = hipMalloc(&ix->pt_pl, sizeof(unsigned short) * plane_elems(dp, dp));
-    if (e == hipSuccess) e = launch_split_t(ix->P, dp, dp, ix->pt_pl, (hipStream_t)stream);
+    if (e == hipSuccess) e = launch_split_t(ix->P, dp, dp, dp, ix->pt_pl, (hipStream_t)stream);
     if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
     if (e != hipSuccess) {
         hipFree(ix->P); hipFree(ix->pt_pl); delete ix;
@@ -627,7 +643,7 @@ int erq_index_load(const char* path, void* stream, erq_index* out)
         if (sz[a]) { if (int rc = file_to_dev(f, dst[a], sz[a], buf, st)) return rc; }
     }
     ERQ_HIP(hipMalloc(&ix->pt_pl, sizeof(unsigned short) * plane_elems(dp, dp)));
-    ERQ_HIP(launch_split_t(ix->P, dp, dp, ix->pt_pl, st));
+    ERQ_HIP(launch_split_t(ix->P, dp, dp, dp, ix->pt_pl, st));
     if (int rc = set_projection_matrix(ix, st)) return rc;
     ERQ_HIP(alloc_cent_planes(ix, st));
     ERQ_HIP(hipStreamSynchronize(st));

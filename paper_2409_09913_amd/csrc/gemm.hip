@@ -402,9 +402,9 @@ hipError_t launch_split_norm(const float* X, int64_t n, int K, unsigned short* p
     return hipGetLastError();
 }
 
-// Planes of the transpose of a K x N row-major matrix (rows j of N), 8
-// consecutive k per thread
-__global__ __launch_bounds__(256) void split_t_kernel(const float* __restrict__ x, int K, int N,
+// Planes of the transpose of N columns of a row-major matrix of K rows ld apart
+// (rows j of N), 8 consecutive k per thread
+__global__ __launch_bounds__(256) void split_t_kernel(const float* __restrict__ x, int K, int ld, int N,
                                                       unsigned short* __restrict__ planes)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -413,17 +413,17 @@ __global__ __launch_bounds__(256) void split_t_kernel(const float* __restrict__ 
     unsigned h[4], l[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c)
-        split2(x[(int64_t)(k + 2 * c) * N + j], x[(int64_t)(k + 2 * c + 1) * N + j], h[c], l[c]);
+        split2(x[(int64_t)(k + 2 * c) * ld + j], x[(int64_t)(k + 2 * c + 1) * ld + j], h[c], l[c]);
     unsigned short* p = planes + plane_at(j, k, K);
     *(uint4*)p = make_uint4(h[0], h[1], h[2], h[3]);
     *(uint4*)(p + 512) = make_uint4(l[0], l[1], l[2], l[3]);
 }
 
-hipError_t launch_split_t(const float* x, int K, int N, unsigned short* planes, hipStream_t st)
+hipError_t launch_split_t(const float* x, int K, int ld, int N, unsigned short* planes, hipStream_t st)
 {
     const int64_t n = (int64_t)(K >> 3) * N;
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(split_t_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, x, K, N, planes);
+    hipLaunchKernelGGL(split_t_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, x, K, ld, N, planes);
     return hipGetLastError();
 }
 
@@ -728,12 +728,13 @@ hipError_t launch_mm(const unsigned short* A, int64_t n, int K, const float* an2
 
 }  // namespace
 
-// out = A.B^T (n x N, leading dimension ldo) from the planes of A (n x K) and B (N x K)
-hipError_t launch_gemm_bf16x3(const unsigned short* A, int64_t n, const unsigned short* B, int64_t N, int K,
-                              float* out, int64_t ldo, hipStream_t st)
+// out = A.(B0 | B1)^T (n x (N0 + N1), leading dimension ldo) from the planes of A
+// (n x K), B0 (N0 x K) and B1 (N1 x K; N1 may be 0)
+hipError_t launch_gemm_bf16x3(const unsigned short* A, int64_t n, const unsigned short* B0, int N0,
+                              const unsigned short* B1, int N1, int K, float* out, int64_t ldo, hipStream_t st)
 {
-    if (n <= 0 || N <= 0) return hipSuccess;
-    return launch_mm(A, n, K, nullptr, MmOut{B, (int)N, 0, out, ldo, nullptr}, MmOut{B, 0, 0, nullptr, 0, nullptr}, st);
+    if (n <= 0 || N0 <= 0) return hipSuccess;
+    return launch_mm(A, n, K, nullptr, MmOut{B0, N0, 0, out, ldo, nullptr}, MmOut{B1, N1, 0, out + N0, ldo, nullptr}, st);
 }
 
 // The probe's distances D (n x N; negated inner products with neg_ip) and,

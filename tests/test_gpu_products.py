@@ -85,6 +85,17 @@ def test_probe_does_not_depend_on_the_batch(n, nl, dp):
         assert torch.equal(p1, probes[lo:lo + 16]) and torch.equal(d1, d[lo:lo + 16]), lo
 
 
+@pytest.mark.parametrize("n,dp", [(10_000, 64), (4100, 128), (1000, 768), (1025, 1024), (200, 4096), (700, 704)])
+def test_rotation_in_turns(n, dp):
+    """Scratch cut in parts (planes of the rows, of P or of both between 2 and 4 MiB) against a few rows at a time."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    x = torch.randn((n, dp), device=DEV, generator=g)
+    P = torch.randn((dp, dp), device=DEV, generator=g)
+    got = erq.rotate(x, P, precision=2)
+    for lo in range(0, n, 61 if n <= 1025 else 499):
+        assert torch.equal(got[lo:lo + 40], erq.rotate(x[lo:lo + 40].contiguous(), P, precision=2)), lo
+
+
 def test_timer_names():
     """"rotate" counts rotations launched by themselves; a search's is part of the probe's launch."""
     g = torch.Generator(device=DEV).manual_seed(5)
