@@ -707,13 +707,15 @@ hipError_t launch_mm_big(const unsigned short* A, int64_t n, int K, const float*
 // 3072: 60 against 240).  Instead of 2 x 1, 128 x 128 tiles where there is one for
 // every CU and K is long: each wave's reading of its fragments from L2 then costs
 // more than the barriers (200 x 16,384 x 4096: 125 us against 221, x 1536: 42
-// against 64).
+// against 64).  Planes that are not 16-byte aligned (in a caller's workspace that
+// is not) keep away from the direct LDS copies.
 hipError_t launch_mm(const unsigned short* A, int64_t n, int K, const float* an2, const MmOut& o0, const MmOut& o1,
                      hipStream_t st)
 {
     const int64_t waves = (n + 63) / 64 * ((o0.N + 63) / 64 + (o1.N + 63) / 64);
     const int64_t cols = (o0.N + 127) / 128 + (o1.N + 127) / 128, rows = (n + 127) / 128;
-    if ((rows + 1) / 2 * cols >= 256) {
+    const bool aligned = (((uintptr_t)A | (uintptr_t)o0.B | (uintptr_t)o1.B) & 15) == 0;
+    if (aligned && (rows + 1) / 2 * cols >= 256) {
         if (n <= 32) return launch_mm_t<1, 1, 1, 8>(A, n, K, an2, o0, o1, st);
         if (n <= 64) return launch_mm_t<1, 1, 2, 8>(A, n, K, an2, o0, o1, st);
         if (rows == 1 || rows == 3) return launch_mm_big<4, 2>(A, n, K, an2, o0, o1, st);
@@ -721,7 +723,7 @@ hipError_t launch_mm(const unsigned short* A, int64_t n, int K, const float* an2
     }
     if (waves >= 2048) return launch_mm_t<2, 2, 2, 2>(A, n, K, an2, o0, o1, st);
     if (n <= 32) return launch_mm_t<1, 1, 1, 8>(A, n, K, an2, o0, o1, st);
-    if (waves >= 900 && K >= (waves >= 1024 ? 1536 : 3072) && rows * cols >= 256) return launch_mm_big<4, 2>(A, n, K, an2, o0, o1, st);
+    if (aligned && waves >= 900 && K >= (waves >= 1024 ? 1536 : 3072) && rows * cols >= 256) return launch_mm_big<4, 2>(A, n, K, an2, o0, o1, st);
     if (waves >= 1024) return launch_mm_t<2, 1, 2, 2>(A, n, K, an2, o0, o1, st);
     return launch_mm_t<1, 1, 2, 8>(A, n, K, an2, o0, o1, st);
 }

@@ -2631,14 +2631,17 @@ int run_scan(Index* ix, const float* qrot, int64_t qld, int64_t nq, const int32_
     // one final select merges them: the same exact top-kk by (est, id).
     // With S below 16 (kk > 256 at nprobe >= 16) each workgroup would keep a
     // long exact list over a large share of the probed members; such calls
-    // take the pipeline.  Two query planes above kMaxDpPlanes2 never do: an item's
-    // queries do not fit the LDS there.
+    // take the pipeline.  Two query planes above kMaxDpPlanes2 never do, as an
+    // item's queries do not fit the LDS there, nor do int8 rows that are not 16-byte
+    // aligned (the caller's workspace is not): the pipeline copies them straight to
+    // the LDS 16 bytes a lane.
     // Fewer than 512 workgroups in all leave compute units idle, so a query is
     // then split into up to 32 parts also when it has fewer lists, as far as its
     // buffer holds kk from each (one query, 16 lists of 200 members: 16 parts
     // 64 us, 32 parts 56 us, 64 parts 59 us: the select reads more).
     const int small_s = std::min(std::min(nprobe, kSmallS), std::max(1, kCapQ / kk));
-    const bool small = (nq <= ix->small_q && small_s >= std::min(nprobe, 16)) || (lo && dp > kMaxDpPlanes2);
+    const bool small = (nq <= ix->small_q && small_s >= std::min(nprobe, 16)) || (lo && dp > kMaxDpPlanes2) ||
+                       ((uintptr_t)qint & 15) != 0;
     const int slices = std::min((int)std::max<int64_t>(small_s, std::min<int64_t>(32, 512 / nq)), std::min(kSmallS, std::max(1, kCapQ / kk)));
     // queries to int8 once; ||s||^2 per pair from the probe distances, else computed
     hipLaunchKernelGGL(qprep_kernel, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, st, qrot, nq, dp, (int)qld, qint,

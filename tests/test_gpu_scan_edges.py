@@ -68,3 +68,21 @@ def test_small_batch_slices(nq, nprobe, kk):
     ix.set_small_batch(0)
     want = ix.search(q, nprobe, kk)
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+def test_workspace_that_is_not_16_byte_aligned():
+    """The same results from a workspace at an odd multiple of 8 bytes."""
+    ix, x, g = make(128, 4)
+    q = x[torch.randint(len(x), (300,), device=DEV, generator=g)] + 0.3 * torch.randn((300, 128), device=DEV, generator=g)
+    c = torch.randn((16_500, 128), device=DEV, generator=g)
+    for nprobe, k in ((5, 10), (18, 100)):
+        want = ix.search(q, nprobe, k)
+        buf = torch.empty(ix.search_workspace_size(300, nprobe, k) + 8, dtype=torch.uint8, device=DEV)
+        got = ix.search(q, nprobe, k, ws=buf[8:])
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    want = erq.coarse_probe(q, c, 20)
+    buf = torch.empty((256 << 20) + 8, dtype=torch.uint8, device=DEV)
+    got = torch.empty_like(want)
+    rc = erq.load().erq_coarse_probe(q.data_ptr(), 300, c.data_ptr(), 16_500, 128, 20, 0, got.data_ptr(), None,
+                                     buf[8:].data_ptr(), 256 << 20, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0 and torch.equal(got, want)
