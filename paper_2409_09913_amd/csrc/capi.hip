@@ -460,7 +460,7 @@ int erq_quantize(const float* rrot, int64_t n, int32_t dp, int32_t bits, const f
                  uint8_t* codes, float* f_add, float* f_rescale, float* cos_oo, void* stream)
 {
     if (int rc = check_dp(dp, "erq_quantize")) return rc;
-    if (dp > 3072) return fail(ERQ_EUNSUPPORTED, "erq_quantize: dp > 3072 exceeds the LDS window");
+    if (dp > 3072) return fail(ERQ_EUNSUPPORTED, "erq_quantize: dp must be at most 3072");
     if (bits < 1 || bits > 8) return fail(ERQ_EUNSUPPORTED, "erq_quantize: bits must be in [1, 8]");
     if (n < 0 || (n > 0 && (!rrot || !codes))) return fail(ERQ_EINVAL, "erq_quantize: null pointer or n < 0");
     int pr = prof_begin(PK_QUANTIZE, (hipStream_t)stream);
@@ -845,7 +845,7 @@ int erq_index_build(erq_index ix, const float* x, int64_t n, const float* centro
         centroids = own_cent;
     }
     if (precision != 0 && precision != 1) return fail(ERQ_EUNSUPPORTED, "erq_index_build: precision must be 0 or 1");
-    if (ix->dp > 3072) return fail(ERQ_EUNSUPPORTED, "erq_index_build: dp > 3072 exceeds the LDS window");
+    if (ix->dp > 3072) return fail(ERQ_EUNSUPPORTED, "erq_index_build: dp must be at most 3072");
     hipStream_t st = (hipStream_t)stream;
     const int64_t C = ix->nlist;
     const int dp = ix->dp, dc = ix->dc;

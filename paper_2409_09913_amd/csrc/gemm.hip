@@ -267,7 +267,11 @@ hipError_t launch_gemm(const float* A, int64_t n, int K, const float* B, int N, 
     dim3 grid((unsigned)((N + BN - 1) / BN), (unsigned)((n + BM - 1) / BM));
     // Few 128 x 128 tiles leave CUs idle behind K / 16 staged steps.  768 x 768,
     // us against the tiles' 71: 1 row 8.5, 128 rows 14, 512 rows 36, 1000 rows 43,
-    // 2,000 rows (96 tiles) 75.  1 x 1 tiles of 16 up to two waves per SIMD.
+    // 2,000 rows (96 tiles) 75.  Other widths, up to the last sizes under 96 tiles:
+    // 128 x 128, 1 to 4,096 rows 7.8 against 15; 1536 x 1536, 100 rows 35, 800 rows
+    // (84 tiles) 126 against 138; 3072 x 3072, 1 row 33, 100 rows 125, 380 rows (72)
+    // 234 against 273; 4096 x 4096, 100 rows 193, 256 rows (64) 295 against 362.
+    // 1 x 1 tiles of 16 up to two waves per SIMD.
     if (precision != 1 && !b_trans && (int64_t)grid.x * grid.y < 96) {
         if ((n + 15) / 16 * ((N + 15) / 16) < 2048) return launch_gemm_small<1, 1, 16>(A, n, K, B, N, out, ldo, st);
         return launch_gemm_small<2, 2, 8>(A, n, K, B, N, out, ldo, st);

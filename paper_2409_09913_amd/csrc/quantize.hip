@@ -62,9 +62,11 @@ constexpr int kWide = 4;             // first pass, many levels: the last bins a
 constexpr int kSortMax = 128;        // events left for the sort (else another pass of bins)
 constexpr int kPasses = 6;           // passes of bins before the windows
 // Events past t = S2/S1 (a <= S1 in units of max a in [1, 2)) cannot raise f:
-// S2 (S1 + a) > 2 t S1^2 fails.  S2 <= 3072 * 255^2 < 2^28 and S1 >= 1, so no
+// S2 (S1 + a) > 2 t S1^2 fails.  S2 <= kMaxDp * 255^2 < 2^28 and S1 >= 1, so no
 // event with key below 2^-28 is ever the maximum.
 constexpr unsigned kMinKey = 0x31800000u;    // bits of 2^-28f
+static_assert((int64_t)kMaxDp * 255 * 255 < (1 << 28), "the bound on S2");
+static_assert(kMaxDp <= 1 << 12, "event_key: the dimension takes 12 bits");
 
 __device__ inline unsigned long long shfl_xor_u64(unsigned long long v, int o) {
     const unsigned lo = (unsigned)__shfl_xor((int)(unsigned)v, o);

@@ -33,7 +33,6 @@
 //  5. fallback: a query whose buffer still overflowed is scanned again in
 //     full by one workgroup that keeps its exact top-kk in LDS.
 #include <algorithm>
-#include <type_traits>
 
 #include "erq_common.h"
 
@@ -352,13 +351,17 @@ __global__ __launch_bounds__(kThreads, 2) void scanB_kernel(
     // next item needs is fetched while the current one is scanned, in three
     // dependent steps of wave 0 (the wave with the fewest tiles): its number
     // (before the scan), its descriptor (before the last group's products) and
-    // the queries of its pairs (before the last group's epilogue).  After the
+    // the queries of its pairs (before the last group's epilogue).  Two of the
+    // steps wait: the counter's atomic is compiled to its wave form, whose result
+    // is read back at once, a round trip at the head of every item, and the
+    // descriptor's components are read behind whatever loads wave 0 has in flight,
+    // its last ring refills among them.  After the
     // item's last barrier everything else is read at once: the int8 query rows,
     // the members' factors and ids, the per-query terms, the first codes and
     // the positions in the candidate buffers of the staged survivors of the
-    // item just ended, so that an item costs one memory latency beside its scan.
-    // (The steps keep their values in vector registers, written in place, so
-    // that none of them waits for its load.)
+    // item just ended, so that an item costs one memory latency beside its scan
+    // and those two.  (The steps keep their values in vector registers, written in
+    // place.)
     int nid = 0, ndv = 0;
     int nq_ = 0, nslot_ = 0, nmq = 0, nmem = 0;
     int64_t nfirst = 0, ntile0 = 0;
@@ -403,7 +406,8 @@ __global__ __launch_bounds__(kThreads, 2) void scanB_kernel(
     // The packed codes of step s + PD are loaded while step s runs: a ring
     // of PD slots of raw words in registers.  PD divides nkb, so the steps come
     // in blocks of PD within one group, and a block loads the words of the next
-    // one; the last block of the item loads nothing.  A slot is refilled only
+    // one; the last block of the item loads its own again, which nobody uses (no
+    // load is conditional).  A slot is refilled only
     // after its unpacking (the scheduling barrier): loads moved above it would
     // need registers of their own, and the copies of those back into the ring
     // would wait for every load in flight, once per block.
@@ -2168,7 +2172,8 @@ __global__ void item_desc_kernel(const int32_t* __restrict__ item_off, const int
 
 // The two steps that follow the list prefix and do not depend on each other,
 // in one launch (a launch of its own costs about 5 us in the stream): the first
-// kPairBlocks workgroups place the pairs, the others write the descriptors.
+// kPairBlocks workgroups place the pairs, the others write the descriptors (and
+// hold the counters' LDS unused).
 __global__ __launch_bounds__(1024) void pair_place_kernel(const int32_t* __restrict__ probes, int64_t np, int nprobe,
                                                           int nlist, int rlo, int rhi,
                                                           const int32_t* __restrict__ cnt2,
@@ -2441,7 +2446,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Scan schedule: the stored value when it is valid for the index, else the
 // built-in rule (two query tiles per item up to dp = 768; ring depth 6 when
 // it divides the K-steps per group and the raw words are small (B <= 4),
-// else the largest of 4, 3, 2, 1 that divides them; 8 ranks in round 1).
+// else the largest of 4, 3, 2, 1 that divides them; kRound1 ranks in round 1).
 int scan_nqt(const Index* ix)
 {
     if (ix->tune_nqt == 1) return 1;
